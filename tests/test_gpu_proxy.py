@@ -181,6 +181,72 @@ def test_gemm_bf16_storage_equals_fp32_operands(dev, P, variant, shape, splits):
             assert torch.equal(act3, act2), (a16, b16)
 
 
+# one or two tiles of each width (32, 64, 128) and their remainders, part k tiles (8, 16, 56, 64, 72, 264 k values:
+# fewer and more than the copies in flight), more than 256 tiles of 32 and of 64, and widths the tiled kernels leave
+# to the register-staged one (a row-contiguous extent of 36)
+@pytest.mark.parametrize("shape,splits", [((8, 8, 8), 1), ((32, 40, 16), 1), ((40, 32, 56), 1), ((64, 72, 64), 1),
+                                          ((136, 200, 72), 1), ((36, 264, 264), 1), ((520, 1032, 200), 1),
+                                          ((2056, 1000, 328), 1), ((264, 136, 520), 4), ((1032, 264, 1096), 16)])
+@pytest.mark.parametrize("variant", [0, 1, 2])
+def test_tiled_products_at_tile_edges(dev, P, variant, shape, splits):
+    """The tiled kernels (BF16 B) against the register-staged one (FP32 B) on
+    the same values: the products, the epilogue and the split sums bit for
+    bit, whatever tile the sizes choose.  Operands and outputs sit in rows
+    padded with NaN, which no product may read and no store may reach."""
+    M, N, K = shape
+    g = torch.Generator(device=dev).manual_seed(M + N + K + variant)
+
+    def padded(rows, cols, dtype):
+        full = torch.full((rows, cols + 8), float("nan"), dtype=dtype, device=dev)
+        full[:, :cols] = torch.randn(rows, cols, generator=g, device=dev).to(torch.bfloat16).to(dtype)
+        return full, cols + 8
+
+    A, lda = padded(*((M, K) if variant != 2 else (K, M)), torch.float32)
+    B, ldb = padded(*((N, K) if variant == 0 else (K, N)), torch.float32)
+    bias = torch.randn(N + 1, generator=g, device=dev)[1:]  # any FP32 address
+    work = torch.empty(max(splits * M * N, 4), device=dev)
+    kinds = [(True, torch.bfloat16), (True, torch.float32)] + ([(False, torch.bfloat16)] if variant != 2 else [])
+    for a16, act_dtype in kinds:
+        out = []
+        for b16 in (False, True):
+            C = torch.full((M, N + 4), float("nan"), device=dev)
+            act = torch.full((M, N + 4), float("nan"), dtype=act_dtype, device=dev)
+            P.gemm_mixed(variant, A.to(torch.bfloat16) if a16 else A, a16, lda, B.to(torch.bfloat16) if b16 else B, b16,
+                         ldb, C, N + 4, M, N, K, bias=bias, act=act, act_bf16=act_dtype == torch.bfloat16,
+                         splits=splits, work=work)
+            D = C.clone()
+            P.gemm_mixed(variant, A.to(torch.bfloat16) if a16 else A, a16, lda, B.to(torch.bfloat16) if b16 else B, b16,
+                         ldb, D, N + 4, M, N, K, accumulate=True, splits=splits, work=work)
+            torch.cuda.synchronize()
+            for t in (C, act, D):
+                assert bool(t[:, N:].isnan().all()) and not bool(t[:, :N].isnan().any())
+            out.append((C, act, D))
+        for x, y in zip(*out):
+            assert torch.equal(x[:, :N], y[:, :N]), (a16, act_dtype)
+
+
+@pytest.mark.parametrize("shape", [(4, 8, 8), (132, 40, 64), (128, 64, 264), (1100, 136, 72), (4104, 1032, 136)])
+@pytest.mark.parametrize("a_bf16", [True, False])
+def test_tiled_gelu_backward_at_tile_edges(dev, P, shape, a_bf16):
+    """prox_gemm_gelu_bwd's tiled kernels (BF16 B) against the register-staged
+    one (FP32 B): output and column sums bit for bit."""
+    M, N, K = shape
+    g = torch.Generator(device=dev).manual_seed(M + N)
+    A = torch.randn(M, K, generator=g, device=dev).to(torch.bfloat16)
+    B = torch.randn(K, N, generator=g, device=dev).to(torch.bfloat16)
+    pre = torch.randn(M, N, generator=g, device=dev) * 2.0
+    A = A if a_bf16 else A.float()
+    out = []
+    for b16 in (False, True):
+        d = torch.full((M, N + 4), float("nan"), dtype=torch.bfloat16, device=dev)
+        part = torch.full((((M + 127) // 128) * N,), float("nan"), device=dev)
+        P.gemm_gelu_bwd(A, a_bf16, K, B if b16 else B.float(), b16, N, pre, N, d, N + 4, M, N, K, part)
+        torch.cuda.synchronize()
+        assert bool(d[:, N:].isnan().all())
+        out.append((d[:, :N], part))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
 def test_gemm_bf16_storage_shape_rules(dev, P):
     from paper_2510_12897_amd.opf import OPFError
     a = torch.zeros(64, 64, device=dev)
