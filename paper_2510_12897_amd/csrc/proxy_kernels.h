@@ -51,18 +51,17 @@ hipError_t prox_wgrad_finish(const float* work, int splits, int M, int N, float*
                              int chunks, int NB, float* bias_out, hipStream_t s);
 // out [M, N] (BF16) = (A B) * gelu'(pre) for row-major A [M, K], B [K, N]
 // (either BF16), pre [M, N]; part [ceil(M / 128), N] = the column sums of
-// each 128-row block of the FP32 product (prox_colsum's first pass); outT
-// (optional) = out transposed, [N, M] with leading dimension ldT (a
-// multiple of 8, outT 16-byte aligned).
+// each 128-row block of the FP32 product (prox_colsum's first pass).
 hipError_t prox_gemm_gelu_bwd(const void* A, bool a_bf16, int lda, const void* B, bool b_bf16, int ldb,
                               const float* pre, int ldp, void* out, int ldo, int M, int N, int K, float* part,
-                              hipStream_t s, void* outT = nullptr, int ldT = 0);
+                              hipStream_t s);
 // out [N] = scale * the column sums of part [chunks, N] (prox_colsum's second pass)
 hipError_t prox_colsum_parts(const float* part, int chunks, int N, float* out, float scale, hipStream_t s);
 hipError_t prox_gelu_bwd(const float* pre, const float* dact, float* dpre, int64_t n, hipStream_t s);
 hipError_t prox_colsum(const float* X, int M, int N, float* part, float* out, float scale, hipStream_t s);
-// prox_colsum's first pass only: part [ceil(M / 128), N]
-hipError_t prox_colsum_first(const float* X, int M, int N, float* part, hipStream_t s);
+// prox_colsum's first pass only: part [ceil(M / 128), N]; Xb (may be NULL)
+// receives X rounded to BF16
+hipError_t prox_colsum_first(const float* X, int M, int N, float* part, void* Xb, hipStream_t s);
 hipError_t prox_adam(float* p, const float* g, float* m1, float* m2, int64_t n, float lr, float b1, float b2, float eps,
                      int step, void* pb, hipStream_t s);
 hipError_t prox_adam_dev(float* p, const float* g, float* m1, float* m2, int64_t n, float lr, float b1, float b2,

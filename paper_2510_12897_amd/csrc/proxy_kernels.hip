@@ -418,7 +418,6 @@ __device__ __forceinline__ void xcd_tile(int& i0, int& j0, int& kz) {
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // Row-major staging of a workgroup's accumulators in LDS (rows SROW floats
 // apart): lane holds column lane % 32 of each 32x32 tile, rows (v / 4) * 8 +
@@ -480,8 +479,10 @@ tile_gemm_kernel(const TA* __restrict__ A, int lda, const TB* __restrict__ B, in
     if (j >= N) return;
     f32x4 bv = {0.f, 0.f, 0.f, 0.f};
     if (bias) bv = (f32x4){bias[j], bias[j + 1], bias[j + 2], bias[j + 3]};
-    // Outputs are streamed past the caches (non-temporal): nothing of this
-    // launch reads them again (4096 x 1024 x 1024 with GELU: 18.3 -> 16.6 us).
+    // Beside an activation, C is the pre-activation that only a much later
+    // backward reads: it is streamed past the caches (non-temporal).  The
+    // outputs the next launch reads are not (the loss over a streamed z took
+    // 96 us, over a cached one 87).
     auto rows = [&](auto to_c, auto act_kind) {  // act_kind: 0 none, 1 FP32, 2 BF16
         auto row = [&](int lr) {
             f32x4 r = *reinterpret_cast<const f32x4*>(stage + lr * SROW + c4 * 4);
@@ -490,16 +491,17 @@ tile_gemm_kernel(const TA* __restrict__ A, int lda, const TB* __restrict__ B, in
             if constexpr (to_c.value) {
                 f32x4* cp = reinterpret_cast<f32x4*>(C + at);
                 if (accumulate) r += *cp;
-                __builtin_nontemporal_store(r, cp);
+                if constexpr (act_kind.value)
+                    __builtin_nontemporal_store(r, cp);
+                else
+                    *cp = r;
             }
             if constexpr (act_kind.value == 2) {
-                const bf16x4 h = {to_bf16(gelu(r[0])), to_bf16(gelu(r[1])), to_bf16(gelu(r[2])), to_bf16(gelu(r[3]))};
-                u32x2 w;
-                __builtin_memcpy(&w, &h, 8);
-                __builtin_nontemporal_store(w, reinterpret_cast<u32x2*>(static_cast<__bf16*>(act) + at));
+                *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(act) + at) =
+                    (bf16x4){to_bf16(gelu(r[0])), to_bf16(gelu(r[1])), to_bf16(gelu(r[2])), to_bf16(gelu(r[3]))};
             } else if constexpr (act_kind.value == 1) {
-                const f32x4 g = {gelu(r[0]), gelu(r[1]), gelu(r[2]), gelu(r[3])};
-                __builtin_nontemporal_store(g, reinterpret_cast<f32x4*>(static_cast<float*>(act) + at));
+                *reinterpret_cast<f32x4*>(static_cast<float*>(act) + at) =
+                    (f32x4){gelu(r[0]), gelu(r[1]), gelu(r[2]), gelu(r[3])};
             }
         };
         if (i0 + BM <= M) {
@@ -583,16 +585,12 @@ tile_gelu_bwd_kernel(const TA* __restrict__ A, int lda, const TB* __restrict__ B
 // colsum_partial_kernel (rows g, g + 4, ... for g = 0..3, then the four
 // groups in order), so the values equal the GEMM, gelu_bwd and colsum
 // kernels in sequence bit for bit.
-// outT (may be NULL) receives d transposed, [N, M] BF16 with leading
-// dimension ldT (a multiple of 8): the k-contiguous operand of the next
-// weight-gradient product.
 template <bool A_KCONT, bool B_KCONT, typename TA, typename TB>
 __global__ void __launch_bounds__(GEMM_THREADS) gemm_gelu_bwd_kernel(const TA* __restrict__ A, int lda,
                                                                      const TB* __restrict__ B, int ldb,
                                                                      const float* __restrict__ pre, int ldp,
                                                                      __bf16* __restrict__ out, int ldo, int M, int N,
-                                                                     int K, float* __restrict__ part,
-                                                                     __bf16* __restrict__ outT, int ldT) {
+                                                                     int K, float* __restrict__ part) {
     constexpr int BN = 64, SROW = BN + 4, C4 = BN / 4;
     // the whole 128 x 64 FP32 tile (padded rows) and the column-sum groups fit the operand tiles' LDS
     static_assert(BM * SROW * 4 + 4 * 64 * 4 <= gemm_smem_bytes<BN>(), "staging tile");
@@ -628,19 +626,6 @@ __global__ void __launch_bounds__(GEMM_THREADS) gemm_gelu_bwd_kernel(const TA* _
     __syncthreads();
     const int c = threadIdx.x % 64, g = threadIdx.x / 64, j = j0 + c;
     const int rows = min(BM, M - i0);
-    if (outT && j < N) {  // 8 consecutive rows of column j per 16-byte store
-        __bf16* tcol = outT + (size_t)j * ldT + i0;
-        for (int r0 = g * 8; r0 < rows; r0 += 32) {
-            if (r0 + 8 <= rows) {
-                bf16x8 v;
-#pragma unroll
-                for (int q = 0; q < 8; q++) v[q] = to_bf16(stage[(r0 + q) * SROW + c]);
-                *reinterpret_cast<bf16x8*>(tcol + r0) = v;
-            } else {
-                for (int q = r0; q < rows; q++) tcol[q] = to_bf16(stage[q * SROW + c]);
-            }
-        }
-    }
     float s = 0.f;
     if (j < N)
         for (int r = g; r < rows; r += 4) s += stage[r * SROW + c];
@@ -703,15 +688,32 @@ __global__ void gelu_bwd_kernel(const float* __restrict__ pre, const float* __re
 // each sum in row order, then the four groups in order.  Pass 2: the chunk
 // sums of each column the same way (chunks g, g + 4, ..., then the groups).
 constexpr int COLSUM_ROWS = 128;
+// Xb (may be NULL): X rounded to BF16, on the way.
 __global__ void __launch_bounds__(256) colsum_partial_kernel(const float* __restrict__ X, int M, int N,
-                                                             float* __restrict__ part) {
+                                                             float* __restrict__ part, __bf16* __restrict__ Xb) {
     __shared__ float s[4][64];
     const int c = threadIdx.x % 64, g = threadIdx.x / 64;
     const int j = blockIdx.x * 64 + c;
     const int i0 = blockIdx.y * COLSUM_ROWS, i1 = min(i0 + COLSUM_ROWS, M);
     float acc = 0.f;
-    if (j < N)
-        for (int i = i0 + g; i < i1; i += 4) acc += X[(size_t)i * N + j];
+    if (j < N) {
+        int i = i0 + g;
+        for (; i + 28 < i1; i += 32) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; u++) v[u] = X[(size_t)(i + 4 * u) * N + j];
+#pragma unroll
+            for (int u = 0; u < 8; u++) {
+                acc += v[u];
+                if (Xb) Xb[(size_t)(i + 4 * u) * N + j] = to_bf16(v[u]);
+            }
+        }
+        for (; i < i1; i += 4) {
+            const float v = X[(size_t)i * N + j];
+            acc += v;
+            if (Xb) Xb[(size_t)i * N + j] = to_bf16(v);
+        }
+    }
     s[g][c] = acc;
     __syncthreads();
     if (g == 0 && j < N) part[(size_t)blockIdx.y * N + j] = ((s[0][c] + s[1][c]) + s[2][c]) + s[3][c];
@@ -866,6 +868,14 @@ __global__ void step_bump_kernel(int32_t* step) { *step += 1; }
 __global__ void to_bf16_kernel(const float* __restrict__ x, int64_t n, __bf16* __restrict__ y) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) y[i] = to_bf16(x[i]);
+}
+
+__global__ void __launch_bounds__(256) to_bf16x8_kernel(const float* __restrict__ x, int64_t n8,
+                                                        __bf16* __restrict__ y) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n8) return;
+    const float4 a = reinterpret_cast<const float4*>(x)[2 * i], b = reinterpret_cast<const float4*>(x)[2 * i + 1];
+    reinterpret_cast<bf16x8*>(y)[i] = pack8(a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w);
 }
 
 __device__ __forceinline__ double sigmoid(double z) { return 1.0 / (1.0 + exp(-z)); }
@@ -1647,31 +1657,28 @@ hipError_t gemm_b(int variant, const TA* A, int lda, const void* B, bool b_bf16,
 namespace {
 template <typename TA, typename TB>
 hipError_t gelu_bwd_typed(const TA* A, int lda, const TB* B, int ldb, const float* pre, int ldp, __bf16* out, int ldo,
-                          int M, int N, int K, float* part, __bf16* outT, int ldT, hipStream_t s) {
+                          int M, int N, int K, float* part, hipStream_t s) {
     hipLaunchKernelGGL((gemm_gelu_bwd_kernel<true, false, TA, TB>), dim3((N + 63) / 64, (M + BM - 1) / BM, 1),
-                       dim3(GEMM_THREADS), 0, s, A, lda, B, ldb, pre, ldp, out, ldo, M, N, K, part, outT, ldT);
+                       dim3(GEMM_THREADS), 0, s, A, lda, B, ldb, pre, ldp, out, ldo, M, N, K, part);
     return hipGetLastError();
 }
 template <typename TA>
 hipError_t gelu_bwd_b(const TA* A, int lda, const void* B, bool b_bf16, int ldb, const float* pre, int ldp, __bf16* out,
-                      int ldo, int M, int N, int K, float* part, __bf16* outT, int ldT, hipStream_t s) {
+                      int ldo, int M, int N, int K, float* part, hipStream_t s) {
     if (b_bf16)
-        return gelu_bwd_typed(A, lda, static_cast<const __bf16*>(B), ldb, pre, ldp, out, ldo, M, N, K, part, outT,
-                              ldT, s);
-    return gelu_bwd_typed(A, lda, static_cast<const float*>(B), ldb, pre, ldp, out, ldo, M, N, K, part, outT, ldT,
-                          s);
+        return gelu_bwd_typed(A, lda, static_cast<const __bf16*>(B), ldb, pre, ldp, out, ldo, M, N, K, part, s);
+    return gelu_bwd_typed(A, lda, static_cast<const float*>(B), ldb, pre, ldp, out, ldo, M, N, K, part, s);
 }
 }  // namespace
 
 hipError_t prox_gemm_gelu_bwd(const void* A, bool a_bf16, int lda, const void* B, bool b_bf16, int ldb,
                               const float* pre, int ldp, void* out, int ldo, int M, int N, int K, float* part,
-                              hipStream_t s, void* outT, int ldT) {
+                              hipStream_t s) {
     __bf16* o = static_cast<__bf16*>(out);
-    __bf16* oT = static_cast<__bf16*>(outT);
     // Column width by the tile_shape rule (the column sums fix 128 rows):
     // 4096 x 1024 x 1024 19.6 us with 64 columns, 21.0 with 128, before 29.4;
     // 1024 rows 10.7 with 32, 11.7 with 64, before 24.9.
-    if (!oT && tiled_product(1, A, a_bf16, lda, B, b_bf16, ldb, M, N, K)) {
+    if (tiled_product(1, A, a_bf16, lda, B, b_bf16, ldb, M, N, K)) {
         const __bf16* b = static_cast<const __bf16*>(B);
         auto go = [&](auto kernel, const auto* a, int cols, int threads) {
             hipLaunchKernelGGL(kernel, dim3((N + cols - 1) / cols, (M + BM - 1) / BM, 1), dim3(threads), 0, s, a, lda, b,
@@ -1693,9 +1700,8 @@ hipError_t prox_gemm_gelu_bwd(const void* A, bool a_bf16, int lda, const void* B
         return hipGetLastError();
     }
     if (a_bf16)
-        return gelu_bwd_b(static_cast<const __bf16*>(A), lda, B, b_bf16, ldb, pre, ldp, o, ldo, M, N, K, part, oT, ldT,
-                          s);
-    return gelu_bwd_b(static_cast<const float*>(A), lda, B, b_bf16, ldb, pre, ldp, o, ldo, M, N, K, part, oT, ldT, s);
+        return gelu_bwd_b(static_cast<const __bf16*>(A), lda, B, b_bf16, ldb, pre, ldp, o, ldo, M, N, K, part, s);
+    return gelu_bwd_b(static_cast<const float*>(A), lda, B, b_bf16, ldb, pre, ldp, o, ldo, M, N, K, part, s);
 }
 
 hipError_t prox_colsum_parts(const float* part, int chunks, int N, float* out, float scale, hipStream_t s) {
@@ -1755,15 +1761,17 @@ hipError_t prox_gelu_bwd(const float* pre, const float* dact, float* dpre, int64
     return hipGetLastError();
 }
 
-hipError_t prox_colsum_first(const float* X, int M, int N, float* part, hipStream_t s) {
+hipError_t prox_colsum_first(const float* X, int M, int N, float* part, void* Xb, hipStream_t s) {
     const int chunks = (M + COLSUM_ROWS - 1) / COLSUM_ROWS;
-    hipLaunchKernelGGL(colsum_partial_kernel, dim3((N + 63) / 64, chunks), dim3(256), 0, s, X, M, N, part);
+    hipLaunchKernelGGL(colsum_partial_kernel, dim3((N + 63) / 64, chunks), dim3(256), 0, s, X, M, N, part,
+                       static_cast<__bf16*>(Xb));
     return hipGetLastError();
 }
 
 hipError_t prox_colsum(const float* X, int M, int N, float* part, float* out, float scale, hipStream_t s) {
     const int chunks = (M + COLSUM_ROWS - 1) / COLSUM_ROWS;
-    hipLaunchKernelGGL(colsum_partial_kernel, dim3((N + 63) / 64, chunks), dim3(256), 0, s, X, M, N, part);
+    hipLaunchKernelGGL(colsum_partial_kernel, dim3((N + 63) / 64, chunks), dim3(256), 0, s, X, M, N, part,
+                       static_cast<__bf16*>(nullptr));
     hipLaunchKernelGGL(colsum_final_kernel, dim3((N + 63) / 64), dim3(256), 0, s, part, chunks, N, out, scale);
     return hipGetLastError();
 }
@@ -1793,6 +1801,12 @@ hipError_t prox_adam_dev(float* p, const float* g, float* m1, float* m2, int64_t
 }
 
 hipError_t prox_to_bf16(const float* x, int64_t n, void* y, hipStream_t s) {
+    // 16-byte loads and stores where the buffers allow them (2.4 M values: 5.2 us)
+    if (n % 8 == 0 && aligned16(x) && aligned16(y)) {
+        hipLaunchKernelGGL(to_bf16x8_kernel, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, s, x, n / 8,
+                           static_cast<__bf16*>(y));
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(to_bf16_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, x, n, static_cast<__bf16*>(y));
     return hipGetLastError();
 }
