@@ -576,9 +576,9 @@ int prox_train_step_bytes(const prox_mlp_desc *mlp, int B, int64_t *bytes);
  * of 8; prox_loss_fused on its output at loads [B, 2N]; the gradient of the
  * mean loss (weight 1/B); the MLP backward (split-K weight gradients, bias
  * column sums, the GELU backward in the dh product as prox_gemm_gelu_bwd);
- * and prox_adam_dev (lr, beta1, beta2, eps).  The same kernels in the same
- * order as those calls made one by one, so the parameters after a step are
- * theirs bit for bit.  loss, cvio [B] receive the per-sample loss and Cvio
+ * and prox_adam_dev's update (lr, beta1, beta2, eps).  The same values as
+ * those calls made one by one, each rounded alike, so the parameters after a
+ * step are theirs bit for bit.  loss, cvio [B] receive the per-sample loss and Cvio
  * before the update.  work: work_bytes of device memory (16-byte aligned,
  * at least prox_train_step_bytes) that the step uses as scratch; the model
  * is one prox_loss_fused takes and the MLP's output width is 2N + 2G;

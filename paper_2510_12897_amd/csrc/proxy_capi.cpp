@@ -83,9 +83,9 @@ struct TrainPlan {
     std::vector<int> fo, fi, splits;
     std::vector<bool> w_bf16, act_bf16;
     std::vector<size_t> pre, act;                 // byte offsets of each layer's pre-activation and activation
-    size_t xb = 0, dz = 0, dzb = 0, gflat = 0, cwork = 0, skw = 0, d0 = 0, d1 = 0, dh = 0, total = 0;
+    std::vector<size_t> gw, gb;                   // its weight gradient's parts and bias gradient's column sums
+    size_t xb = 0, dz = 0, dzb = 0, d0 = 0, d1 = 0, dh = 0, total = 0;
     bool x_bf16 = false, dz_bf16 = false;         // BF16 copies of the features and of d loss / d z are kept
-    int64_t n_params = 0;
 };
 
 int make_plan(const prox_mlp_desc* mlp, int B, TrainPlan& P) {
@@ -106,7 +106,6 @@ int make_plan(const prox_mlp_desc* mlp, int B, TrainPlan& P) {
         if (d < 4 || d % 4) return set_err(OPF_E_ARG, "layer widths must be positive multiples of 4");
         P.maxd = std::max(P.maxd, d);
     }
-    size_t sk = 4;
     for (int k = 0; k < P.nl; k++) {
         const int fi = mlp->dims[k], fo = mlp->dims[k + 1];
         P.fi.push_back(fi);
@@ -120,11 +119,11 @@ int make_plan(const prox_mlp_desc* mlp, int B, TrainPlan& P) {
         P.act_bf16.push_back(k < P.nl - 1 && mlp->flat_bf16 != nullptr && fo % 8 == 0);
         const int sp = opf::prox_gemm_splits(fo, fi, B);
         P.splits.push_back(sp);
-        if (sp > 1) sk = std::max(sk, (size_t)sp * fo * fi);
+        P.gw.push_back(take(sizeof(float) * (size_t)sp * fo * fi));
+        P.gb.push_back(take(sizeof(float) * (size_t)P.chunks * fo));
         P.pre.push_back(take(sizeof(float) * (size_t)B * fo));
         P.act.push_back(k < P.nl - 1 ? take((P.act_bf16.back() ? 2 : 4) * (size_t)B * fo) : 0);
     }
-    P.n_params = par;
     P.D = mlp->dims[P.nl];
     P.dz = take(sizeof(float) * (size_t)B * P.D);
     // rounded once where the products would each round them (and the tiled
@@ -133,9 +132,6 @@ int make_plan(const prox_mlp_desc* mlp, int B, TrainPlan& P) {
     P.dz_bf16 = mlp->flat_bf16 != nullptr && P.D % 8 == 0;
     if (P.x_bf16) P.xb = take(2 * (size_t)B * mlp->dims[0]);
     if (P.dz_bf16) P.dzb = take(2 * (size_t)B * P.D);
-    P.gflat = take(sizeof(float) * (size_t)par);
-    P.cwork = take(sizeof(float) * (size_t)P.chunks * P.maxd);
-    P.skw = take(sizeof(float) * sk);
     P.d0 = take(sizeof(float) * (size_t)B * P.maxd);
     P.d1 = take(sizeof(float) * (size_t)B * P.maxd);
     P.dh = take(sizeof(float) * (size_t)B * P.maxd);
@@ -229,63 +225,66 @@ int prox_train_step(opf_model model, const prox_mlp_desc* mlp, const float* feat
     float* dz = reinterpret_cast<float*>(W + P.dz);
     const opf::ProxPerm pm{model->he_pos, model->gen_pos};
     // d loss / d z scaled by the mean's 1/B and rounded to FP32 by the loss kernel itself, then the top
-    // layer's bias sums' first pass over it
+    // layer's bias sums' first pass over it (which also moves Adam's step count on)
     if (!ok(opf::prox_loss_fused(model->dm, box_of(model, va_span), rows_of(model), pm, z, loads, B, rho, obj_scale,
                                  loss, cvio, nullptr, nullptr, nullptr, s, dz, 1.0 / B)) ||
-        !ok(opf::prox_colsum_first(dz, B, P.D, reinterpret_cast<float*>(W + P.cwork),
-                                   P.dz_bf16 ? W + P.dzb : nullptr, s)))
+        !ok(opf::prox_colsum_first(dz, B, P.D, reinterpret_cast<float*>(W + P.gb[P.nl - 1]),
+                                   P.dz_bf16 ? W + P.dzb : nullptr, mlp->step, s)))
         return hip_err(e, "prox_train_step loss");
     pe.mark(2, s);
-    // backward: weight gradients (split over the batch), bias column sums and
-    // the GELU backward of the layer below in the dh product
-    float* gflat = reinterpret_cast<float*>(W + P.gflat);
-    float* cwork = reinterpret_cast<float*>(W + P.cwork);
-    float* skw = reinterpret_cast<float*>(W + P.skw);
+    // backward: weight gradients (split over the batch), the bias column
+    // sums' first pass and the GELU backward of the layer below in the dh product
     const void* dpre = P.dz_bf16 ? (const void*)(W + P.dzb) : dz;
-    bool d_bf16 = P.dz_bf16, parts = true;  // the top layer's column sums' first pass came with dz
+    bool d_bf16 = P.dz_bf16;
     char* dbuf[2] = {W + P.d0, W + P.d1};
     for (int k = P.nl - 1; k >= 0; k--) {
         const int fo = P.fo[k], fi = P.fi[k];
         const void* h_in = k == 0 ? x_in : (const void*)(W + P.act[k - 1]);
         const bool h_in_bf16 = k == 0 ? P.x_bf16 : P.act_bf16[k - 1];
-        if (P.splits[k] > 1 && parts) {
-            // the split-K parts, then their sum and the bias sums' second pass in one launch
-            if (!ok(opf::prox_gemm_split_parts(2, dpre, d_bf16, fo, h_in, h_in_bf16, fi, fo, fi, B, P.splits[k], skw,
-                                               s)) ||
-                !ok(opf::prox_wgrad_finish(skw, P.splits[k], fo, fi, gflat + P.wo[k], fi, cwork, P.chunks, fo,
-                                           gflat + P.bo[k], s)))
-                return hip_err(e, "prox_train_step weight and bias gradients");
-        } else {
-            if (!ok(opf::prox_gemm_mixed(2, dpre, d_bf16, fo, h_in, h_in_bf16, fi, gflat + P.wo[k], fi, fo, fi, B,
-                                         nullptr, nullptr, false, 0, P.splits[k], skw, s)))
-                return hip_err(e, "prox_train_step weight gradient");
-            if (!ok(parts ? opf::prox_colsum_parts(cwork, P.chunks, fo, gflat + P.bo[k], 1.0f, s)
-                          : opf::prox_colsum(static_cast<const float*>(dpre), B, fo, cwork, gflat + P.bo[k], 1.0f,
-                                             s)))
-                return hip_err(e, "prox_train_step bias gradient");
-        }
+        float* gw = reinterpret_cast<float*>(W + P.gw[k]);
+        if (!ok(P.splits[k] > 1 ? opf::prox_gemm_split_parts(2, dpre, d_bf16, fo, h_in, h_in_bf16, fi, fo, fi, B,
+                                                             P.splits[k], gw, s)
+                                : opf::prox_gemm_mixed(2, dpre, d_bf16, fo, h_in, h_in_bf16, fi, gw, fi, fo, fi, B,
+                                                       nullptr, nullptr, false, 0, 1, nullptr, s)))
+            return hip_err(e, "prox_train_step weight gradient");
         if (k == 0) break;
         const float* pre_below = reinterpret_cast<const float*>(W + P.pre[k - 1]);
+        float* gb = reinterpret_cast<float*>(W + P.gb[k - 1]);
         char* d = dbuf[k & 1];
         if (fi % 8 == 0) {
             if (!ok(opf::prox_gemm_gelu_bwd(dpre, d_bf16, fo, weight(k), P.w_bf16[k], fi, pre_below, fi, d, fi, B, fi,
-                                            fo, cwork, s)))
+                                            fo, gb, s)))
                 return hip_err(e, "prox_train_step dh");
-            d_bf16 = parts = true;
+            d_bf16 = true;
         } else {
             float* dh = reinterpret_cast<float*>(W + P.dh);
             if (!ok(opf::prox_gemm_mixed(1, dpre, d_bf16, fo, weight(k), P.w_bf16[k], fi, dh, fi, B, fi, fo, nullptr,
                                          nullptr, false, 0, 1, nullptr, s)) ||
-                !ok(opf::prox_gelu_bwd(pre_below, dh, reinterpret_cast<float*>(d), (int64_t)B * fi, s)))
+                !ok(opf::prox_gelu_bwd(pre_below, dh, reinterpret_cast<float*>(d), (int64_t)B * fi, s)) ||
+                !ok(opf::prox_colsum_first(reinterpret_cast<float*>(d), B, fi, gb, nullptr, nullptr, s)))
                 return hip_err(e, "prox_train_step dh");
-            d_bf16 = parts = false;
+            d_bf16 = false;
         }
         dpre = d;
     }
     pe.mark(3, s);
-    if (!ok(opf::prox_adam_dev(mlp->flat, gflat, mlp->m1, mlp->m2, P.n_params, lr, beta1, beta2, eps, mlp->step,
-                               mlp->flat_bf16, s)))
-        return hip_err(e, "prox_train_step Adam");
+    // the gradients' sums and Adam, kUpdateLayers layers a launch
+    for (int k0 = 0; k0 < P.nl; k0 += opf::kUpdateLayers) {
+        opf::UpdateLayers u{};
+        u.n = std::min(P.nl - k0, opf::kUpdateLayers);
+        u.chunks = P.chunks;
+        for (int q = 0; q < u.n; q++) {
+            opf::UpdateLayer& L = u.layer[q];
+            L.wo = P.wo[k0 + q];
+            L.fo = P.fo[k0 + q];
+            L.fi = P.fi[k0 + q];
+            L.splits = P.splits[k0 + q];
+            L.work = reinterpret_cast<const float*>(W + P.gw[k0 + q]);
+            L.part = reinterpret_cast<const float*>(W + P.gb[k0 + q]);
+        }
+        if (!ok(opf::prox_update(u, mlp->flat, mlp->m1, mlp->m2, mlp->flat_bf16, lr, beta1, beta2, eps, mlp->step, s)))
+            return hip_err(e, "prox_train_step Adam");
+    }
     if (phase_ms) {
         pe.mark(4, s);
         if (pe.err != hipSuccess) return hip_err(pe.err, "prox_train_step phase events");

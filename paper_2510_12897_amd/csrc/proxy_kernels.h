@@ -45,10 +45,25 @@ int prox_gemm_splits(int M, int N, int K);
 // activation or accumulation: work receives splits * M * N floats.
 hipError_t prox_gemm_split_parts(int variant, const void* A, bool a_bf16, int lda, const void* B, bool b_bf16, int ldb,
                                  int M, int N, int K, int splits, float* work, hipStream_t s);
-// C [M, N] = the split-K parts summed in order, and bias_out [NB] = the
-// column sums of part [chunks, NB] (prox_colsum's second pass), one launch.
-hipError_t prox_wgrad_finish(const float* work, int splits, int M, int N, float* C, int ldc, const float* part,
-                             int chunks, int NB, float* bias_out, hipStream_t s);
+// One layer of the training step's parameter update: weight [fo, fi] at
+// offset wo of the parameters, its bias behind it; the weight gradient's
+// split-K parts (work: splits * fo * fi floats, 16-byte aligned) and the bias
+// gradient's first column-sum pass (part: [chunks, fo]).
+struct UpdateLayer {
+    int64_t wo;
+    const float *work, *part;
+    int32_t fo, fi, splits;
+    int32_t first, weight_blocks;  // set by prox_update
+};
+constexpr int kUpdateLayers = 8;
+struct UpdateLayers {
+    int32_t n, chunks;
+    UpdateLayer layer[kUpdateLayers];
+};
+// Gradient sums and Adam of those layers; *step is this step's count (from 1);
+// pb (may be NULL, 8-byte aligned) receives the BF16 copy.
+hipError_t prox_update(UpdateLayers u, float* p, float* m1, float* m2, void* pb, float lr, float b1, float b2, float eps,
+                       const int32_t* step, hipStream_t s);
 // out [M, N] (BF16) = (A B) * gelu'(pre) for row-major A [M, K], B [K, N]
 // (either BF16), pre [M, N]; part [ceil(M / 128), N] = the column sums of
 // each 128-row block of the FP32 product (prox_colsum's first pass).
@@ -60,8 +75,8 @@ hipError_t prox_colsum_parts(const float* part, int chunks, int N, float* out, f
 hipError_t prox_gelu_bwd(const float* pre, const float* dact, float* dpre, int64_t n, hipStream_t s);
 hipError_t prox_colsum(const float* X, int M, int N, float* part, float* out, float scale, hipStream_t s);
 // prox_colsum's first pass only: part [ceil(M / 128), N]; Xb (may be NULL)
-// receives X rounded to BF16
-hipError_t prox_colsum_first(const float* X, int M, int N, float* part, void* Xb, hipStream_t s);
+// receives X rounded to BF16; *count (may be NULL) is moved on by one
+hipError_t prox_colsum_first(const float* X, int M, int N, float* part, void* Xb, int32_t* count, hipStream_t s);
 hipError_t prox_adam(float* p, const float* g, float* m1, float* m2, int64_t n, float lr, float b1, float b2, float eps,
                      int step, void* pb, hipStream_t s);
 hipError_t prox_adam_dev(float* p, const float* g, float* m1, float* m2, int64_t n, float lr, float b1, float b2,

@@ -1027,6 +1027,32 @@ def test_native_training_step_equals_the_autograd_step(dev, P, width, depth, bf1
     b.close()
 
 
+@pytest.mark.parametrize("N,width,depth,B,shift", [(14, 24, 8, 64, 0), (14, 64, 2, 1536, 1), (18, 36, 1, 132, 3),
+                                                     (300, 40, 7, 68, 0)])
+def test_update_pass_layers_splits_and_addresses(dev, P, N, width, depth, B, shift):
+    """The step's one pass of gradient sums and Adam against the autograd
+    path's separate kernels, bit for bit: nine layers (two launches) and
+    eight, weight gradients in one part and in several, output widths that
+    are and are not multiples of 8 (BF16 and FP32 d loss / d z), moments at
+    16-byte and at 4-byte addresses."""
+    case = _case(N=N, L=N + 6, G=6, seed=3)
+    a, b = _twin_proxies(P, case, B, width, depth, True)
+    for px in (a, b):
+        for name in ("m1", "m2"):
+            t = torch.zeros(px.mlp.n_params + shift, device=dev)[shift:]
+            setattr(px.mlp, name, t)
+    gen = torch.Generator(device=dev).manual_seed(7)
+    for _ in range(2):
+        loads, feats = a.sample(gen)
+        assert torch.equal(a.train_step(loads, feats, lr=1e-3), b.train_step(loads, feats, lr=1e-3))
+    torch.cuda.synchronize()
+    for t0, t1 in ((a.mlp.flat.detach(), b.mlp.flat.detach()), (a.mlp.m1, b.mlp.m1), (a.mlp.m2, b.mlp.m2),
+                   (a.mlp.step_dev, b.mlp.step_dev), (a.mlp.flat_bf16, b.mlp.flat_bf16)):
+        assert torch.equal(t0, t1)
+    a.close()
+    b.close()
+
+
 def test_native_training_step_at_benchmark_size(dev, P):
     """The benchmarked proxy (300 buses, MLP 600 -> 3 x 1024 -> 720, 4,096
     samples): two native steps equal two autograd steps bit for bit, and
