@@ -38,20 +38,11 @@ import math
 import numpy as np
 
 from . import opf
-from .opf import OPF_E_ARG, OPFError, _check, lib
-
-
-def _torch():
-    import torch
-    return torch
+from .opf import OPF_E_ARG, OPFError, _check, _stream, _torch, lib
 
 
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
-
-
-def _stream():
-    return ctypes.c_void_p(_torch().cuda.current_stream().cuda_stream)
+    return None if t is None else t.data_ptr()
 
 
 def gemm(variant, A, lda, B, ldb, C, ldc, M, N, K, bias=None, act=None, accumulate=False, splits=1, work=None):
@@ -146,9 +137,13 @@ class MLP:
         The forward reads it k-contiguous, so a BF16 copy needs its input
         width a multiple of 8; other layers read the FP32 buffer."""
         wo, bo, fo, fi = self.layout[k]
-        if self.bf16_storage and fi % 8 == 0:
+        if self.weight_bf16(k):
             return self.flat_bf16[wo:wo + fo * fi].view(fo, fi), True
         return self.weight(k), False
+
+    def weight_bf16(self, k):
+        """Whether the matrix cores read layer k's weights from the BF16 copy."""
+        return self.bf16_storage and self.layout[k][3] % 8 == 0
 
     def act_bf16(self, k):
         """Whether hidden layer k stores its activations as BF16 (the next
@@ -221,6 +216,13 @@ def _make_mlp_function():
             acts, pres = [x], []
             h = x
             nl = len(mlp.layout)
+            # the layers' parameters by address (4 or 2 bytes an element): the
+            # products of a small batch end before views of them are built
+            for t in (mlp.flat, mlp.flat_bf16):
+                if t is not None and (t.numel() < mlp.n_params or not t.is_contiguous()):
+                    raise OPFError(OPF_E_ARG, f"the parameters must be {mlp.n_params} contiguous elements")
+            gemm, stream = lib().prox_gemm_bf16_mixed, _stream()
+            w32, w16 = mlp.flat.data_ptr(), mlp.flat_bf16.data_ptr() if mlp.bf16_storage else 0
             for k in range(nl):
                 wo, bo, fo, fi = mlp.layout[k]
                 # a hidden layer's FP32 pre-activation serves only the backward
@@ -229,9 +231,9 @@ def _make_mlp_function():
                 act = None
                 if k < nl - 1:
                     act = torch.empty(Bn, fo, dtype=torch.bfloat16 if ab else torch.float32, device=x.device)
-                W, w_bf16 = mlp.mma_weight(k)
-                gemm_mixed(0, h, h.dtype == torch.bfloat16, fi, W, w_bf16, fi, pre, fo, Bn, fo, fi, bias=mlp.bias(k),
-                           act=act, act_bf16=ab)
+                w_bf16 = mlp.weight_bf16(k)
+                _check(gemm(0, h.data_ptr(), int(h.dtype == torch.bfloat16), fi, w16 + 2 * wo if w_bf16 else w32 + 4 * wo,
+                            int(w_bf16), fi, _p(pre), fo, Bn, fo, fi, w32 + 4 * bo, _p(act), int(ab), 0, 1, None, stream))
                 pres.append(pre)
                 h = act if act is not None else pre
                 if act is not None:

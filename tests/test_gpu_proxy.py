@@ -1122,3 +1122,25 @@ def test_trained_proxy_gains_over_flat_start(dev, P):
     assert curve[0.05] == float(np.mean(cp > 0.05))
     assert all(a >= b for a, b in zip(list(curve.values()), list(curve.values())[1:]))
     px.close()
+
+
+def test_launches_follow_the_current_stream_and_check_the_parameters():
+    import torch
+    from paper_2510_12897_amd import opf as binding, proxy
+    side = torch.cuda.Stream()
+    assert (binding._stream() or 0) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert binding._stream() == side.cuda_stream != torch.cuda.default_stream().cuda_stream
+    mlp = proxy.MLP(8, 4, width=16, depth=1, seed=3)
+    x = torch.randn(4, 8, device="cuda")
+    want = mlp(x).detach()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        got = mlp(x).detach()
+    side.synchronize()
+    assert torch.equal(got, want)
+    whole = mlp.flat
+    for bad in (whole.detach()[:-1], whole.detach().repeat_interleave(2)[::2]):
+        mlp.flat = bad
+        with pytest.raises(binding.OPFError):
+            mlp(x)
