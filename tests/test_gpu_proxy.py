@@ -1144,3 +1144,53 @@ def test_launches_follow_the_current_stream_and_check_the_parameters():
         mlp.flat = bad
         with pytest.raises(binding.OPFError):
             mlp(x)
+
+
+@pytest.mark.parametrize("N,B", [(8, 3), (14, 513), (100, 1), (100, 512), (100, 513), (370, 2)])
+def test_penalty_rows_and_threads(N, B):
+    """Fewer rows than threads, more, and several rounds with a remainder, on
+    both sides of the thread counts' rule: loss within m roundings, the
+    largest violation and the weights exactly (the same operations)."""
+    import ctypes
+    import torch
+    from paper_2510_12897_amd import opf as binding
+    cs = synth.network(N, N * 13 // 10, max(2, N // 5), 7)
+    md = binding.Model(cs)
+    g = torch.Generator(device="cuda").manual_seed(N + B)
+    C = torch.randn(B, md.m, dtype=torch.float64, device="cuda", generator=g)
+    X = torch.randn(B, md.n, dtype=torch.float64, device="cuda", generator=g)
+    F = torch.randn(B, dtype=torch.float64, device="cuda", generator=g)
+    L, rho, osc = cs["n_branch"], 10.0, 1e-3
+    bd = {k: v if torch.is_tensor(v) else torch.as_tensor(v) for k, v in md.bounds().items()}
+    bd = {k: v.to("cuda") for k, v in bd.items()}
+    new = lambda *sh: torch.empty(*sh, dtype=torch.float64, device="cuda")
+    st = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+
+    def call(vjp):
+        pen, cv, W, gpq = new(B), new(B), new(B, md.m), new(B, 4 * L)
+        binding._check(binding.lib().prox_penalty(md.handle, C.data_ptr(), X.data_ptr(), F.data_ptr(), osc, rho, B, vjp,
+                                                  pen.data_ptr(), cv.data_ptr(), W.data_ptr(), gpq.data_ptr(), st))
+        return pen, cv, W, gpq
+
+    def viol(v, lo, hi):
+        return torch.where(v < lo, v - lo, torch.where(v > hi, v - hi, torch.zeros_like(v)))
+
+    dv = viol(C, bd["lcon"], bd["ucon"])
+    o, k = md.block("p")
+    dq = viol(X[:, o:o + 4 * L], bd["lvar"][o:o + 4 * L], bd["uvar"][o:o + 4 * L])
+    flow = torch.zeros(md.m, dtype=torch.bool, device="cuda")
+    for name in ("p_fr", "q_fr", "p_to", "q_to"):
+        o, k = md.block(name)
+        flow[o:o + k] = True
+    pen, cv, W, gpq = call(0)
+    off = torch.where(flow, torch.zeros_like(dv), dv)
+    want = rho * ((off ** 2).sum(1) + (dq ** 2).sum(1)) + osc * F
+    assert ((pen - want).abs() <= (md.m + 4 * L + 4) * 2.2e-16 * (want + 2 * osc * F.abs())).all()
+    assert torch.equal(cv, torch.maximum(dv.abs().amax(1), dq.abs().amax(1)))
+    assert torch.equal(W, 2.0 * rho * off) and torch.equal(gpq, 2.0 * rho * dq)
+    Wt = new(B, md.m)
+    binding._check(binding.lib().prox_vjp_weights(md.handle, X.data_ptr(), W.data_ptr(), gpq.data_ptr(), B,
+                                                  Wt.data_ptr(), st))
+    pen2, cv2, W2, gpq2 = call(1)
+    assert torch.equal(pen2, pen) and torch.equal(cv2, cv) and torch.equal(gpq2, gpq) and torch.equal(W2, Wt)
+    md.close()
