@@ -7,6 +7,7 @@
 #include <tuple>
 
 #include "internal.h"
+#include "proxy_kernels.h"
 
 namespace opf_internal {
 
@@ -206,6 +207,28 @@ int launch_set(opf_model m, const opf::EvalOut& o, void* stream) {
 }  // namespace
 
 // ======================================================================== API
+// Branch parameters of the proxy's fused loss, packed as ProxPerm::br says,
+// at offset off; the angle bounds from the filled constraint bounds at lcon, ucon.
+static void pack_fused_branches(const opf::HostModel& hm, const opf_case* cs, Packer& pk, size_t off, size_t lcon,
+                                size_t ucon) {
+    const opf::Layout& ly = hm.ly;
+    const size_t L = (size_t)ly.L;
+    double2* pair = reinterpret_cast<double2*>(pk.at(off));
+    int4* idx = reinterpret_cast<int4*>(pair + 6 * L);
+    const double* lo = reinterpret_cast<const double*>(pk.at(lcon)) + ly.c_blk[opf::B_ANG];
+    const double* hi = reinterpret_cast<const double*>(pk.at(ucon)) + ly.c_blk[opf::B_ANG];
+    for (size_t l = 0; l < L; l++) {
+        for (size_t k = 0; k < 4; k++) pair[k * L + l] = {hm.coef[2 * k * L + l], hm.coef[(2 * k + 1) * L + l]};
+        pair[4 * L + l] = {lo[l], hi[l]};
+        pair[5 * L + l] = {cs->rate_a[l], hm.rate2[l]};
+        idx[l] = {hm.f_bus[l], hm.t_bus[l], 0, 0};
+    }
+    for (size_t h = 0; h < hm.he.size(); h++) {
+        int4& e = idx[hm.he[h] >> 1];
+        ((hm.he[h] & 1) ? e.z : e.w) = (int32_t)h;
+    }
+}
+
 extern "C" {
 
 const char* opf_last_error(void) { return last_error().c_str(); }
@@ -303,16 +326,15 @@ int opf_model_create(const opf_case* cs, const opf_opts* opts, int device, opf_m
         const size_t ob_lc = pk.reserve(sizeof(double) * ly.m()), ob_uc = pk.reserve(sizeof(double) * ly.m());
         const size_t ob_x0 = pk.reserve(sizeof(double) * ly.n);
         const size_t o_isref = pk.add(m->hm.is_ref);
-        std::vector<int32_t> he_pos(2 * (size_t)ly.L), gen_pos(ly.G);
-        for (size_t h = 0; h < m->hm.he.size(); h++) {
-            const int32_t code = m->hm.he[h];
-            he_pos[((code & 1) ? 0 : ly.L) + (code >> 1)] = (int32_t)h;
-        }
+        std::vector<int32_t> gen_pos(ly.G);
         for (size_t q = 0; q < m->hm.gen_list.size(); q++) gen_pos[m->hm.gen_list[q]] = (int32_t)q;
-        const size_t o_hepos = pk.add(he_pos), o_genpos = pk.add(gen_pos);
+        const size_t o_genpos = pk.add(gen_pos);
         opf::fill_bounds(cs, opts, m->hm, reinterpret_cast<double*>(pk.at(ob_lv)),
                          reinterpret_cast<double*>(pk.at(ob_uv)), reinterpret_cast<double*>(pk.at(ob_lc)),
                          reinterpret_cast<double*>(pk.at(ob_uc)), reinterpret_cast<double*>(pk.at(ob_x0)));
+        const bool fuse = ly.nrep == 1 && !ly.rect && opf::prox_loss_fused_size(ly.N, ly.L, ly.G);
+        const size_t o_br = pk.reserve(fuse ? sizeof(double2) * 7 * (size_t)ly.L : 0);
+        if (fuse) pack_fused_branches(m->hm, cs, pk, o_br, ob_lc, ob_uc);
 
         DeviceGuard dg(device);
         if (dg.err != hipSuccess) {
@@ -343,7 +365,7 @@ int opf_model_create(const opf_case* cs, const opf_opts* opts, int device, opf_m
         m->ucon = reinterpret_cast<const double*>(base + ob_uc);
         m->x0 = reinterpret_cast<const double*>(base + ob_x0);
         m->is_ref = reinterpret_cast<const int32_t*>(base + o_isref);
-        m->he_pos = reinterpret_cast<const int32_t*>(base + o_hepos);
+        if (fuse) m->fuse_br = reinterpret_cast<const double2*>(base + o_br);
         m->gen_pos = reinterpret_cast<const int32_t*>(base + o_genpos);
     } catch (const std::bad_alloc&) {
         delete m;

@@ -63,13 +63,12 @@ opf::ProxRows rows_of(opf_model m) {
 // The fused loss kernel's conditions beyond a static polar model: no storage
 // units or devices, x in the order (va, vm, pg, qg, p, q), and one sample's
 // working set within 64 KiB of LDS.
-constexpr size_t kFusedLdsMax = 65536;
 bool fused_fits(opf_model m) {
     const opf::Layout& ly = m->hm.ly;
     const int64_t N = ly.N, G = ly.G, L = ly.L;
     return ly.nrep == 1 && !ly.rect && ly.S == 0 && ly.D == 0 && ly.x_va == 0 && ly.x_vm == N &&
            ly.x_pg == 2 * N && ly.x_qg == 2 * N + G && ly.x_p == 2 * N + 2 * G && ly.x_q == ly.x_p + 2 * L &&
-           opf::prox_loss_fused_lds(ly.N, ly.L, ly.G) <= kFusedLdsMax;
+           opf::prox_loss_fused_size(ly.N, ly.L, ly.G) && m->fuse_br;
 }
 
 
@@ -223,7 +222,7 @@ int prox_train_step(opf_model model, const prox_mlp_desc* mlp, const float* feat
     // the loss with d loss / d z, then the mean's weight 1/B
     const float* z = reinterpret_cast<const float*>(W + P.pre[P.nl - 1]);
     float* dz = reinterpret_cast<float*>(W + P.dz);
-    const opf::ProxPerm pm{model->he_pos, model->gen_pos};
+    const opf::ProxPerm pm{model->fuse_br, model->gen_pos};
     // d loss / d z scaled by the mean's 1/B and rounded to FP32 by the loss kernel itself, then the top
     // layer's bias sums' first pass over it (which also moves Adam's step count on)
     if (!ok(opf::prox_loss_fused(model->dm, box_of(model, va_span), rows_of(model), pm, z, loads, B, rho, obj_scale,
@@ -497,9 +496,9 @@ int prox_loss_fused(opf_model model, const float* z, int B, double va_span, cons
     if (!fused_fits(model))
         return set_err(OPF_E_ARG, "the fused loss takes a model without storage or devices whose sample fits "
                                   "%zu bytes of LDS",
-                       kFusedLdsMax);
+                       opf::kFusedLdsMax);
     DeviceGuard dg(model->device);
-    const opf::ProxPerm pm{model->he_pos, model->gen_pos};
+    const opf::ProxPerm pm{model->fuse_br, model->gen_pos};
     return launched(opf::prox_loss_fused(model->dm, box_of(model, va_span), rows_of(model), pm, z, loads, B, rho,
                                          obj_scale, loss, cvio, gz, X, C, static_cast<hipStream_t>(stream)),
                     "prox_loss_fused launch");

@@ -106,10 +106,15 @@ hipError_t prox_loss_bwd(const float* z, int B, const ProxBox& box, const ProxOb
 // computed); X [B, n], C [B, m] on request (NULL: not written).  loads [B, 2N]
 // holds each sample's pd then qd.
 struct ProxPerm {
-    const int32_t* he_pos;   // [2L] position of (side, branch) in the bus-ordered half-edge list, from sides first
+    const double2* br;       // [7][L] of 16 bytes: (Gff, Bff), (Gft, Bft), (Gtt, Btt), (Gtf, Btf), angle bounds,
+                             // (rate, rate^2), then int4 (from bus, to bus, their half-edges' positions)
     const int32_t* gen_pos;  // [G] position of generator k in the bus-ordered generator list
 };
-size_t prox_loss_fused_lds(int N, int L, int G);
+// Whether the fused loss takes a network of this size: its working set, with
+// two more values per branch, within 64 KiB (two workgroups per compute unit;
+// beyond, the chain of batch launches fills the chip better).
+constexpr size_t kFusedLdsMax = 65536;
+bool prox_loss_fused_size(int N, int L, int G);
 // dz (optional, in place of gz) = (float)(w * d loss_b / d z_b).
 hipError_t prox_loss_fused(const DevModel& m, const ProxBox& box, const ProxRows& rows, const ProxPerm& pm,
                            const float* z, const double* loads, int B, double rho, double obj_scale, double* loss,

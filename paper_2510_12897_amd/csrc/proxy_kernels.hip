@@ -935,6 +935,13 @@ __global__ void __launch_bounds__(256) to_bf16x8_kernel(const float* __restrict_
     reinterpret_cast<bf16x8*>(y)[i] = pack8(a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w);
 }
 
+// p[i] from a uniform base and a 32-bit byte offset (one address instruction
+// instead of a 64-bit sum per lane; the arrays are far below 4 GiB).
+template <typename T>
+__device__ __forceinline__ T at(const T* p, uint32_t i) {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + i * (uint32_t)sizeof(T));
+}
+
 __device__ __forceinline__ double sigmoid(double z) { return 1.0 / (1.0 + exp(-z)); }
 
 // Entry e < 2N + 2G (va, vm, pg, qg blocks of x) of the squashed network
@@ -944,22 +951,22 @@ __device__ __forceinline__ double sigmoid(double z) { return 1.0 / (1.0 + exp(-z
 __device__ __forceinline__ double squash_entry(const ProxBox& box, const float* zb, int e, double& act) {
     const int N = box.N, G = box.G;
     if (e < N) {  // va
-        act = tanh((double)zb[N + e]);
-        return box.is_ref[e] ? 0.0 : box.va_span * act;
+        act = tanh((double)at(zb, N + e));
+        return at(box.is_ref, e) ? 0.0 : box.va_span * act;
     }
     if (e < 2 * N) {  // vm
         const int i = e - N;
-        act = sigmoid((double)zb[i]);
-        return box.vmin[i] + (box.vmax[i] - box.vmin[i]) * act;
+        act = sigmoid((double)at(zb, i));
+        return at(box.vmin, i) + (at(box.vmax, i) - at(box.vmin, i)) * act;
     }
     if (e < 2 * N + G) {
         const int k = e - 2 * N;
-        act = sigmoid((double)zb[2 * N + k]);
-        return box.pmin[k] + (box.pmax[k] - box.pmin[k]) * act;
+        act = sigmoid((double)at(zb, 2 * N + k));
+        return at(box.pmin, k) + (at(box.pmax, k) - at(box.pmin, k)) * act;
     }
     const int k = e - 2 * N - G;
-    act = sigmoid((double)zb[2 * N + G + k]);
-    return box.qmin[k] + (box.qmax[k] - box.qmin[k]) * act;
+    act = sigmoid((double)at(zb, 2 * N + G + k));
+    return at(box.qmin, k) + (at(box.qmax, k) - at(box.qmin, k)) * act;
 }
 
 // z [B, 2N + 2G] (vm, va, pg, qg blocks, FP32) -> the first 2N + 2G entries
@@ -1254,8 +1261,6 @@ __global__ void sample_loads_kernel(const double* __restrict__ r, const double* 
 // the batch launches bit for bit; the per-bus and per-sample sums are
 // ordered differently (rounding-level differences in the balance rows, the
 // loss and the gradient).
-constexpr int kFuseThreads = 256;
-
 // F = al u^2 + be w^2 + u w (a C + b S) and its derivatives in u, w and the
 // angle difference (the expression of the callback kernels' flow terms).
 struct PFlow {
@@ -1288,103 +1293,75 @@ __device__ __forceinline__ double wave_max64(double v) {
     return v;
 }
 
-// The four flows of branch l at the voltages in LDS: p_f, q_f, p_t, q_t,
-// with cos and sin of the angle difference in C, S (computed here when
-// TRIG, else taken as given).
+// Branch l's packed values (ProxPerm::br).
+struct BranchCoef {
+    double2 ff, ft, tt, tf;  // (G, B) of each side pair
+};
+__device__ __forceinline__ double2 branch_pair(const double2* br, int L, int k, uint32_t l) {
+    return at(br + (size_t)k * L, l);
+}
+__device__ __forceinline__ BranchCoef branch_coef(const double2* br, int L, uint32_t l) {
+    return {branch_pair(br, L, 0, l), branch_pair(br, L, 1, l), branch_pair(br, L, 2, l), branch_pair(br, L, 3, l)};
+}
+
+// The four flows of a branch at end voltages u, w and angle difference (C, S).
 struct BranchFlows {
     PFlow pf, qf, pt, qt;
-    int fb, tb;
 };
-template <bool TRIG>
-__device__ __forceinline__ BranchFlows branch_flows(const DevModel& m, int l, const double* s_va, const double* s_vm,
-                                                    double& C, double& S) {
-    const int L = m.L;
+__device__ __forceinline__ BranchFlows branch_flows(const BranchCoef& k, double u, double w, double C, double S) {
     BranchFlows r;
-    r.fb = m.f_bus[l];
-    r.tb = m.t_bus[l];
-    const double* k = m.coef + l;  // Gff Bff Gft Bft Gtt Btt Gtf Btf, L apart
-    const double Gff = k[0], Bff = k[L], Gft = k[2 * L], Bft = k[3 * L];
-    const double Gtt = k[4 * L], Btt = k[5 * L], Gtf = k[6 * L], Btf = k[7 * L];
-    const double u = s_vm[r.fb], w = s_vm[r.tb];
-    if (TRIG) sincos(s_va[r.fb] - s_va[r.tb], &S, &C);
-    r.pf = pflow(Gff, 0.0, Gft, Bft, u, w, C, S);
-    r.qf = pflow(-Bff, 0.0, -Bft, Gft, u, w, C, S);
-    r.pt = pflow(0.0, Gtt, Gtf, -Btf, u, w, C, S);
-    r.qt = pflow(0.0, -Btt, -Btf, -Gtf, u, w, C, S);
+    r.pf = pflow(k.ff.x, 0.0, k.ft.x, k.ft.y, u, w, C, S);
+    r.qf = pflow(-k.ff.y, 0.0, -k.ft.y, k.ft.x, u, w, C, S);
+    r.pt = pflow(0.0, k.tt.x, k.tf.x, -k.tf.y, u, w, C, S);
+    r.qt = pflow(0.0, -k.tt.y, -k.tf.y, -k.tf.x, u, w, C, S);
     return r;
 }
 
-// What one branch contributes to the penalty, from its arc values in LDS
-// (half-edge positions hf, ht): the thermal, angle and arc-bound
-// violations.  A pass over the branches in two loops, the flows first (with
-// the trigonometry) and then this, holds fewer registers than one loop
-// doing both, so more workgroups fit per compute unit.
-struct ArcPen {
-    double arc[4];  // p_f, p_t, q_f, q_t (x's order)
-    double cf, ct, ca, dvf, dvt, dva, dq[4];
-    int hf, ht;     // positions of the from / to half-edge in the bus-ordered list
+// What the gradient pass needs of a branch, kept in registers from the first
+// pass: its end voltages, cos and sin of its angle difference, d loss / d its arc values (p_f,
+// p_t, q_f, q_t) without the balance rows, the angle row's weight, and its end
+// buses and half-edge positions.
+struct BranchKeep {
+    double u, w, C, S, ap[4], wa;
+    int4 id;
 };
-__device__ __forceinline__ ArcPen arc_pen(const DevModel& m, const ProxRows& rows, const ProxPerm& pm, int l,
-                                          const double* s_va, const double* s_hp, const double* s_hq) {
-#pragma clang fp contract(off)
-    const int L = m.L;
-    ArcPen r;
-    r.hf = pm.he_pos[l];
-    r.ht = pm.he_pos[L + l];
-    const int fb = m.f_bus[l], tb = m.t_bus[l];
-    const double rate2 = m.rate2[l];
-    const double lf = rows.lcon[m.c_thf + l], uf = rows.ucon[m.c_thf + l];
-    const double lt = rows.lcon[m.c_tht + l], ut = rows.ucon[m.c_tht + l];
-    const double la = rows.lcon[m.c_ang + l], ua = rows.ucon[m.c_ang + l];
-    double lo[4], hi[4];
-#pragma unroll
-    for (int a = 0; a < 4; a++) {
-        lo[a] = rows.lvar[rows.pq0 + a * L + l];
-        hi[a] = rows.uvar[rows.pq0 + a * L + l];
-    }
-    r.arc[0] = s_hp[r.hf];
-    r.arc[1] = s_hp[r.ht];
-    r.arc[2] = s_hq[r.hf];
-    r.arc[3] = s_hq[r.ht];
-    r.cf = r.arc[0] * r.arc[0] + r.arc[2] * r.arc[2] - rate2;
-    r.ct = r.arc[1] * r.arc[1] + r.arc[3] * r.arc[3] - rate2;
-    r.ca = s_va[fb] - s_va[tb];
-    r.dvf = viol(r.cf, lf, uf);
-    r.dvt = viol(r.ct, lt, ut);
-    r.dva = viol(r.ca, la, ua);
-#pragma unroll
-    for (int a = 0; a < 4; a++) r.dq[a] = viol(r.arc[a], lo[a], hi[a]);
-    return r;
-}
 
-// LDS (doubles): va, vm [N each]; pg, qg [G each] in the bus-ordered
-// generator list's order; p and q of each half-edge [2L each] in the
+// LDS, in pairs read and written by 16 bytes: (va, vm) [N]; (pg, qg) [G] in
+// the bus-ordered generator list's order; (p, q) of each half-edge [2L] in the
 // bus-ordered half-edge list's order (later the half-edge gradient terms
-// d/dva and d/dvm), so that a bus sums one contiguous range; the
-// balance-row weights [2N]; the squashing activations [2N + 2G] (z's order)
-// and cos, sin of each branch's angle difference [2L], which the gradient
-// pass reuses; three partials per wave.  Sums run in the adjacency and
-// generator-list orders.
-__global__ void __launch_bounds__(kFuseThreads) loss_fused_kernel(DevModel m, ProxBox box, ProxRows rows,
-                                                                  ProxPerm pm, const float* __restrict__ z,
-                                                                  const double* __restrict__ loads, double rho,
-                                                                  double obj_scale, double* __restrict__ loss,
-                                                                  double* __restrict__ cvio, double* __restrict__ gz,
-                                                                  double* __restrict__ X, double* __restrict__ C,
-                                                                  float* __restrict__ dz, double w) {
+// d/dva, d/dvm), so that a bus sums one contiguous range; the balance rows'
+// weights [N]; then the squashing activations [2N + 2G] (z's order) and three
+// partials per wave.  Sums run in the adjacency and generator-list orders.
+//
+// Bound by its FP64 and address instructions (half of a SIMD's time), then by
+// the latency of each phase.  A thread owns KR branches (L <= NT * KR) and
+// carries what the gradient pass needs of them in registers over the
+// barriers; each branch's parameters are packed for 16-byte loads, with only
+// the bounds that a static model can have (fill_bounds: arcs within +-rate,
+// thermal rows in (-inf, 0], balance rows 0).
+// Buses go to the threads from the last one down: the last waves have the
+// fewest branches.  4096 samples of 300 buses and 406 branches: 82.3 us with
+// the branch parameters in separate arrays, read in three passes; 57 with
+// them packed and kept; 53.1 with pairs in LDS; 51.4 with the buses turned
+// (its instructions alone take 32).  Loading ahead of the barriers (102
+// registers) 57.2; one branch per thread in workgroups of 448 73.0.  64
+// samples: 13.1 -> 7.7 us.
+template <int NT, int KR>
+__global__ void __launch_bounds__(NT) loss_fused_kernel(DevModel m, ProxBox box, ProxRows rows, ProxPerm pm,
+                                                        const float* __restrict__ z, const double* __restrict__ loads,
+                                                        double rho, double obj_scale, double* __restrict__ loss,
+                                                        double* __restrict__ cvio, double* __restrict__ gz,
+                                                        double* __restrict__ X, double* __restrict__ C,
+                                                        float* __restrict__ dz, double w) {
 #pragma clang fp contract(off)
-    extern __shared__ double lds[];
+    extern __shared__ double2 lds2[];
     const int N = m.N, L = m.L, G = m.G, D = 2 * N + 2 * G;
-    double* s_va = lds;
-    double* s_vm = s_va + N;
-    double* s_pg = s_vm + N;
-    double* s_qg = s_pg + G;
-    double* s_hp = s_qg + G;
-    double* s_hq = s_hp + 2 * L;
-    double* s_wb = s_hq + 2 * L;
-    double* s_act = s_wb + 2 * N;
-    double* s_cs = s_act + D;
-    double* s_red = s_cs + 2 * L;
+    double2* s_v = lds2;
+    double2* s_g = s_v + N;
+    double2* s_h = s_g + G;
+    double2* s_wb = s_h + 2 * L;
+    double* s_act = reinterpret_cast<double*>(s_wb + N);
+    double* s_red = s_act + D;
     const int tid = threadIdx.x;
     const int64_t b = blockIdx.x;
     const float* zb = z + b * D;
@@ -1393,64 +1370,76 @@ __global__ void __launch_bounds__(kFuseThreads) loss_fused_kernel(DevModel m, Pr
     const double* pdb = loads + b * 2 * N;
     double pen = 0.0, fobj = 0.0, vio = 0.0;
 
-    for (int e = tid; e < D; e += kFuseThreads) {
-        const int pos = e < 2 * N ? e : (e < 2 * N + G ? 2 * N + pm.gen_pos[e - 2 * N]
-                                                       : 2 * N + G + pm.gen_pos[e - 2 * N - G]);
+    for (int e = tid; e < D; e += NT) {
+        // entry e of (va, vm, pg, qg): the half of pair (e - first) or of the generator's position
+        const int pair = e < 2 * N ? (e < N ? e : e - N)
+                                   : N + at(pm.gen_pos, e < 2 * N + G ? e - 2 * N : e - 2 * N - G);
+        const int half = e < 2 * N ? e >= N : e >= 2 * N + G;
         double act;
         const double v = squash_entry(box, zb, e, act);
-        lds[pos] = v;
+        reinterpret_cast<double*>(s_v)[2 * pair + half] = v;
         s_act[e < N ? N + e : (e < 2 * N ? e - N : e)] = act;
         if (xb) xb[e] = v;
     }
     __syncthreads();
 
-    // branches: arc flows (and cos, sin for the gradient pass), then the
-    // angle and thermal rows and the arc bounds
-    for (int l = tid; l < L; l += kFuseThreads) {
-        double Cc, Sc;
-        const BranchFlows f = branch_flows<true>(m, l, s_va, s_vm, Cc, Sc);
-        const int hf = pm.he_pos[l], ht = pm.he_pos[L + l];
-        s_cs[l] = Cc;
-        s_cs[L + l] = Sc;
-        s_hp[hf] = f.pf.F;
-        s_hp[ht] = f.pt.F;
-        s_hq[hf] = f.qf.F;
-        s_hq[ht] = f.qt.F;
-        if (xb) {
-            xb[rows.pq0 + l] = f.pf.F;
-            xb[rows.pq0 + L + l] = f.pt.F;
-            xb[rows.pq0 + 2 * L + l] = f.qf.F;
-            xb[rows.pq0 + 3 * L + l] = f.qt.F;
-        }
-    }
-    for (int l = tid; l < L; l += kFuseThreads) {  // the same thread's branches: no barrier needed
-        const ArcPen r = arc_pen(m, rows, pm, l, s_va, s_hp, s_hq);
-        pen += r.dvf * r.dvf;
-        pen += r.dvt * r.dvt;
-        pen += r.dva * r.dva;
-        vio = fmax(vio, fmax(fabs(r.dvf), fmax(fabs(r.dvt), fabs(r.dva))));
+    // branches: arc flows, the angle and thermal rows, the arc bounds
+    const bool grad = gz || dz;
+    BranchKeep keep[KR];
+#pragma unroll
+    for (int r = 0; r < KR; r++) {
+        const uint32_t l = tid + r * NT;
+        if (l >= (uint32_t)L) break;
+        BranchKeep& t = keep[r];
+        t.id = at(reinterpret_cast<const int4*>(pm.br + (size_t)6 * L), l);
+        const BranchCoef k = branch_coef(pm.br, L, l);
+        const double2 ang = branch_pair(pm.br, L, 4, l), rate = branch_pair(pm.br, L, 5, l);
+        const double2 vf = s_v[t.id.x], vt = s_v[t.id.y];
+        const double ca = vf.x - vt.x;
+        t.u = vf.y;
+        t.w = vt.y;
+        sincos(ca, &t.S, &t.C);
+        const BranchFlows f = branch_flows(k, t.u, t.w, t.C, t.S);
+        s_h[t.id.z] = {f.pf.F, f.qf.F};
+        s_h[t.id.w] = {f.pt.F, f.qt.F};
+        const double arc[4] = {f.pf.F, f.pt.F, f.qf.F, f.qt.F};  // x's order
+        const double cf = arc[0] * arc[0] + arc[2] * arc[2] - rate.y;
+        const double ct = arc[1] * arc[1] + arc[3] * arc[3] - rate.y;
+        const double dvf = cf > 0.0 ? cf : 0.0, dvt = ct > 0.0 ? ct : 0.0, dva = viol(ca, ang.x, ang.y);
+        pen += dvf * dvf;
+        pen += dvt * dvt;
+        pen += dva * dva;
+        vio = fmax(vio, fmax(dvf, fmax(dvt, fabs(dva))));
+        t.wa = 2.0 * rho * dva;
+        const double wth[2] = {2.0 * rho * dvf, 2.0 * rho * dvt};
 #pragma unroll
         for (int a = 0; a < 4; a++) {
-            pen += r.dq[a] * r.dq[a];
-            vio = fmax(vio, fabs(r.dq[a]));
+            const double dq = viol(arc[a], -rate.x, rate.x);
+            pen += dq * dq;
+            vio = fmax(vio, fabs(dq));
+            t.ap[a] = 2.0 * arc[a] * wth[a & 1] + 2.0 * rho * dq;
+        }
+        if (xb) {
+#pragma unroll
+            for (int a = 0; a < 4; a++) xb[rows.pq0 + a * L + l] = arc[a];
         }
         if (cb) {  // flow rows: p - F(v) with p := F(v), exactly 0
             cb[m.c_pfr + l] = 0.0;
             cb[m.c_qfr + l] = 0.0;
             cb[m.c_pto + l] = 0.0;
             cb[m.c_qto + l] = 0.0;
-            cb[m.c_ang + l] = r.ca;
-            cb[m.c_thf + l] = r.cf;
-            cb[m.c_tht + l] = r.ct;
+            cb[m.c_ang + l] = ca;
+            cb[m.c_thf + l] = cf;
+            cb[m.c_tht + l] = ct;
         }
     }
     // objective terms and reference rows
-    for (int k = tid; k < G; k += kFuseThreads) {
-        const double pg = s_pg[pm.gen_pos[k]];
-        fobj += m.c2[k] * pg * pg + m.c1[k] * pg + m.c0[k];
+    for (int k = NT - 1 - tid; k < G; k += NT) {
+        const double pg = s_g[at(pm.gen_pos, k)].x;
+        fobj += at(m.c2, k) * pg * pg + at(m.c1, k) * pg + at(m.c0, k);
     }
-    for (int q = tid; q < m.R; q += kFuseThreads) {
-        const double c = s_va[m.ref_bus[q]];
+    for (int q = tid; q < m.R; q += NT) {
+        const double c = s_v[m.ref_bus[q]].x;
         const double dv = viol(c, rows.lcon[m.c_ref + q], rows.ucon[m.c_ref + q]);
         pen += dv * dv;
         vio = fmax(vio, fabs(dv));
@@ -1459,28 +1448,27 @@ __global__ void __launch_bounds__(kFuseThreads) loss_fused_kernel(DevModel m, Pr
     __syncthreads();
 
     // buses: balance rows, summed over contiguous half-edge and generator ranges
-    for (int i = tid; i < N; i += kFuseThreads) {
-        const int h0 = m.adj_ptr[i], h1 = m.adj_ptr[i + 1], g0 = m.gen_ptr[i], g1 = m.gen_ptr[i + 1];
-        const double gs = m.gs[i], bs = m.bs[i], pd = pdb[i], qd = pdb[N + i];
-        const double lp = rows.lcon[m.c_balp + i], up = rows.ucon[m.c_balp + i];
-        const double lq = rows.lcon[m.c_balq + i], uq = rows.ucon[m.c_balq + i];
-        const double vm = s_vm[i], v2 = vm * vm;
+    for (int i = NT - 1 - tid; i < N; i += NT) {
+        const int h0 = at(m.adj_ptr, i), h1 = at(m.adj_ptr, i + 1), g0 = at(m.gen_ptr, i), g1 = at(m.gen_ptr, i + 1);
+        const double gs = at(m.gs, i), bs = at(m.bs, i), pd = at(pdb, i), qd = at(pdb, N + i);
+        const double vm = s_v[i].y, v2 = vm * vm;
         double sp = 0.0, sq = 0.0;
         for (int h = h0; h < h1; h++) {
-            sp += s_hp[h];
-            sq += s_hq[h];
+            const double2 v = s_h[h];
+            sp += v.x;
+            sq += v.y;
         }
         double cp = pd + gs * v2 + sp, cq = qd - bs * v2 + sq;
         for (int q = g0; q < g1; q++) {
-            cp -= s_pg[q];
-            cq -= s_qg[q];
+            const double2 v = s_g[q];
+            cp -= v.x;
+            cq -= v.y;
         }
-        const double dvp = viol(cp, lp, up), dvq = viol(cq, lq, uq);
+        const double dvp = viol(cp, 0.0, 0.0), dvq = viol(cq, 0.0, 0.0);
         pen += dvp * dvp;
         pen += dvq * dvq;
         vio = fmax(vio, fmax(fabs(dvp), fabs(dvq)));
-        s_wb[i] = 2.0 * rho * dvp;
-        s_wb[N + i] = 2.0 * rho * dvq;
+        s_wb[i] = {2.0 * rho * dvp, 2.0 * rho * dvq};
         if (cb) {
             cb[m.c_balp + i] = cp;
             cb[m.c_balq + i] = cq;
@@ -1497,7 +1485,7 @@ __global__ void __launch_bounds__(kFuseThreads) loss_fused_kernel(DevModel m, Pr
     __syncthreads();  // also: every balance weight written, every half-edge value read
     if (tid == 0) {
         double P = 0.0, F = 0.0, V = 0.0;
-        for (int w = 0; w < kFuseThreads / 64; w++) {
+        for (int w = 0; w < NT / 64; w++) {
             P += s_red[3 * w];
             F += s_red[3 * w + 1];
             V = fmax(V, s_red[3 * w + 2]);
@@ -1505,35 +1493,22 @@ __global__ void __launch_bounds__(kFuseThreads) loss_fused_kernel(DevModel m, Pr
         loss[b] = rho * P + obj_scale * F;
         cvio[b] = V;
     }
-    if (!gz && !dz) return;
+    if (!grad) return;
 
-    // branches: d loss / d arc without the balance rows, in place of each
-    // branch's own arc values; then with the balance rows, carried through
-    // p = F(v) to the branch's four voltage entries, per half-edge
-    for (int l = tid; l < L; l += kFuseThreads) {
-        const ArcPen r = arc_pen(m, rows, pm, l, s_va, s_hp, s_hq);
-        const double wth[2] = {2.0 * rho * r.dvf, 2.0 * rho * r.dvt};
-        double ap[4];
+    // branches: d loss / d arc with the balance rows, carried through p = F(v)
+    // to the branch's four voltage entries, per half-edge
 #pragma unroll
-        for (int a = 0; a < 4; a++) ap[a] = 2.0 * r.arc[a] * wth[a & 1] + 2.0 * rho * r.dq[a];
-        s_hp[r.hf] = ap[0];
-        s_hp[r.ht] = ap[1];
-        s_hq[r.hf] = ap[2];
-        s_hq[r.ht] = ap[3];
-    }
-    for (int l = tid; l < L; l += kFuseThreads) {
-        double Cc = s_cs[l], Sc = s_cs[L + l];
-        const BranchFlows f = branch_flows<false>(m, l, s_va, s_vm, Cc, Sc);
-        const int hf = pm.he_pos[l], ht = pm.he_pos[L + l];
-        const double la = rows.lcon[m.c_ang + l], ua = rows.ucon[m.c_ang + l];
-        const double wa = 2.0 * rho * viol(s_va[f.fb] - s_va[f.tb], la, ua);
-        const double tpf = s_hp[hf] + s_wb[f.fb], tpt = s_hp[ht] + s_wb[f.tb];
-        const double tqf = s_hq[hf] + s_wb[N + f.fb], tqt = s_hq[ht] + s_wb[N + f.tb];
+    for (int r = 0; r < KR; r++) {
+        const uint32_t l = tid + r * NT;
+        if (l >= (uint32_t)L) break;
+        const BranchKeep& t = keep[r];
+        const BranchFlows f = branch_flows(branch_coef(pm.br, L, l), t.u, t.w, t.C, t.S);
+        const double2 wf = s_wb[t.id.x], wt = s_wb[t.id.y];
+        const double tpf = t.ap[0] + wf.x, tpt = t.ap[1] + wt.x;
+        const double tqf = t.ap[2] + wf.y, tqt = t.ap[3] + wt.y;
         const double gt = tpf * f.pf.Ft + tqf * f.qf.Ft + tpt * f.pt.Ft + tqt * f.qt.Ft;
-        s_hp[hf] = gt + wa;
-        s_hp[ht] = -(gt + wa);
-        s_hq[hf] = tpf * f.pf.Fu + tqf * f.qf.Fu + tpt * f.pt.Fu + tqt * f.qt.Fu;
-        s_hq[ht] = tpf * f.pf.Fw + tqf * f.qf.Fw + tpt * f.pt.Fw + tqt * f.qt.Fw;
+        s_h[t.id.z] = {gt + t.wa, tpf * f.pf.Fu + tqf * f.qf.Fu + tpt * f.pt.Fu + tqt * f.qt.Fu};
+        s_h[t.id.w] = {-(gt + t.wa), tpf * f.pf.Fw + tqf * f.qf.Fw + tpt * f.pt.Fw + tqt * f.qt.Fw};
     }
     __syncthreads();
     // d loss / d z in FP64, or (dz) as (float)(w * d loss / d z): the scaling
@@ -1544,30 +1519,33 @@ __global__ void __launch_bounds__(kFuseThreads) loss_fused_kernel(DevModel m, Pr
         else
             gz[b * D + j] = v;
     };
-    for (int i = tid; i < N; i += kFuseThreads) {
-        const int h0 = m.adj_ptr[i], h1 = m.adj_ptr[i + 1];
-        const double gs = m.gs[i], bs = m.bs[i];
-        const double span_v = box.vmax[i] - box.vmin[i];
-        const int ref = box.is_ref[i];
+    for (int i = NT - 1 - tid; i < N; i += NT) {
+        const int h0 = at(m.adj_ptr, i), h1 = at(m.adj_ptr, i + 1);
+        const double gs = at(m.gs, i), bs = at(m.bs, i);
+        const double span_v = at(box.vmax, i) - at(box.vmin, i);
+        const int ref = at(box.is_ref, i);
         double ga = 0.0, gm = 0.0;
         for (int h = h0; h < h1; h++) {
-            ga += s_hp[h];
-            gm += s_hq[h];
+            const double2 v = s_h[h];
+            ga += v.x;
+            gm += v.y;
         }
-        const double vm = s_vm[i];
-        gm += 2.0 * gs * vm * s_wb[i] - 2.0 * bs * vm * s_wb[N + i];
+        const double vm = s_v[i].y;
+        const double2 wb = s_wb[i];
+        gm += 2.0 * gs * vm * wb.x - 2.0 * bs * vm * wb.y;
         const double s = s_act[i];
         put(i, gm * span_v * s * (1.0 - s));
         const double t = s_act[N + i];
         put(N + i, ref ? 0.0 : ga * box.va_span * (1.0 - t * t));
     }
-    for (int k = tid; k < G; k += kFuseThreads) {
-        const int bus = m.gen_bus[k], q = pm.gen_pos[k];
-        const double gp = -s_wb[bus] + obj_scale * (2.0 * m.c2[k] * s_pg[q] + m.c1[k]);
-        const double gq = -s_wb[N + bus];
+    for (int k = tid; k < G; k += NT) {
+        const int bus = at(m.gen_bus, k), q = at(pm.gen_pos, k);
+        const double2 wb = s_wb[bus];
+        const double gp = -wb.x + obj_scale * (2.0 * at(m.c2, k) * s_g[q].x + at(m.c1, k));
+        const double gq = -wb.y;
         const double sp = s_act[2 * N + k], sq = s_act[2 * N + G + k];
-        put(2 * N + k, gp * (box.pmax[k] - box.pmin[k]) * sp * (1.0 - sp));
-        put(2 * N + G + k, gq * (box.qmax[k] - box.qmin[k]) * sq * (1.0 - sq));
+        put(2 * N + k, gp * (at(box.pmax, k) - at(box.pmin, k)) * sp * (1.0 - sp));
+        put(2 * N + G + k, gq * (at(box.qmax, k) - at(box.qmin, k)) * sq * (1.0 - sq));
     }
 }
 
@@ -1965,15 +1943,39 @@ hipError_t prox_vjp_weights(const double* X, const double* W, const double* gpq,
 }
 
 
-size_t prox_loss_fused_lds(int N, int L, int G) {
-    return sizeof(double) * ((size_t)6 * N + 4 * (size_t)G + 6 * (size_t)L + 3 * (kFuseThreads / 64));
+namespace {
+template <int NT, int KR>
+void launch_loss_fused(const DevModel& m, const ProxBox& box, const ProxRows& rows, const ProxPerm& pm, const float* z,
+                       const double* loads, int B, double rho, double obj_scale, double* loss, double* cvio, double* gz,
+                       double* X, double* C, hipStream_t s, float* dz, double w) {
+    const size_t lds = sizeof(double) * ((size_t)6 * m.N + 4 * (size_t)m.G + 4 * (size_t)m.L + 3 * (NT / 64));
+    hipLaunchKernelGGL((loss_fused_kernel<NT, KR>), dim3(B), dim3(NT), lds, s, m, box, rows, pm, z, loads, rho,
+                       obj_scale, loss, cvio, gz, X, C, dz, w);
+}
+}  // namespace
+
+bool prox_loss_fused_size(int N, int L, int G) {
+    return sizeof(double) * ((size_t)6 * N + 4 * (size_t)G + 6 * (size_t)L + 12) <= kFusedLdsMax;  // so L < 1366
 }
 
 hipError_t prox_loss_fused(const DevModel& m, const ProxBox& box, const ProxRows& rows, const ProxPerm& pm,
                            const float* z, const double* loads, int B, double rho, double obj_scale, double* loss,
                            double* cvio, double* gz, double* X, double* C, hipStream_t s, float* dz, double w) {
-    hipLaunchKernelGGL(loss_fused_kernel, dim3(B), dim3(kFuseThreads), prox_loss_fused_lds(m.N, m.L, m.G), s, m, box,
-                       rows, pm, z, loads, rho, obj_scale, loss, cvio, gz, X, C, dz, w);
+    // Two branches per thread keep the most workgroups on a compute unit; up
+    // to two samples per unit one branch per thread ends sooner (300 buses, 406
+    // branches: 64 samples 7.7 us, 9.3 with two; 512 11.2 and 12.1; 1024 17.4
+    // and 17.6; 4096 54.6 and 51.0).  Beyond 512 branches both are even while
+    // the batch is small and two win after (541 branches, 4096 samples: 81.7,
+    // 120 with one).  Up to 64 branches, one wave per sample once a unit has
+    // more than four (14 buses, 4096 samples: 12.4 us against 19.6 with 256
+    // threads; 1024: 7.8 and 8.1; 64: 7.3 and 6.7).
+    auto* launch = m.L <= 64 && B > 4 * kUnits    ? launch_loss_fused<64, 1>
+                   : m.L <= 256                   ? launch_loss_fused<256, 1>
+                   : m.L <= 512 && B <= 2 * kUnits ? launch_loss_fused<512, 1>
+                   : m.L <= 512                   ? launch_loss_fused<256, 2>
+                   : m.L <= 1024                  ? launch_loss_fused<512, 2>
+                                                  : launch_loss_fused<1024, 2>;
+    launch(m, box, rows, pm, z, loads, B, rho, obj_scale, loss, cvio, gz, X, C, s, dz, w);
     return hipGetLastError();
 }
 

@@ -1194,3 +1194,39 @@ def test_penalty_rows_and_threads(N, B):
     pen2, cv2, W2, gpq2 = call(1)
     assert torch.equal(pen2, pen) and torch.equal(cv2, cv) and torch.equal(gpq2, gpq) and torch.equal(W2, Wt)
     md.close()
+
+
+@pytest.mark.parametrize("N,L,B", [(14, 64, 1025), (14, 64, 1024), (14, 65, 1025), (60, 256, 3), (60, 257, 512),
+                                   (60, 257, 513), (60, 512, 514), (60, 513, 2), (60, 1024, 2), (60, 1025, 2)])
+def test_fused_loss_branches_per_thread(dev, P, N, L, B):
+    """Both sides of each line of the launch's rule (threads per sample,
+    branches per thread) against the chain of batch launches: x, the arc
+    flows, thermal and angle rows bit for bit, balance rows, loss, Cvio and dz
+    to rounding."""
+    case = synth.network(N, L, 6, 11)
+    px = P.WarmStartProxy(case, B=B, width=16, depth=1, rho=10.0, obj_scale=1e-3, seed=2)
+    assert px.pen.fused
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(N + L + B)
+    loads, _ = px.sample(gen)
+    z = (torch.randn(B, 2 * px.N + 2 * px.G, generator=gen, device=dev) * 1.5).requires_grad_(True)
+    wb = torch.rand(B, generator=gen, device=dev, dtype=torch.float64) + 0.5
+    out = []
+    for fused in (True, False):
+        px.pen.fused = fused
+        z.grad = None
+        lb = P._fun("loss").apply(z, px, loads, True)
+        (lb * wb).sum().backward()
+        out.append((lb.detach().clone(), px.pen.last["x"].clone(), px.pen.last["c"].view(B, -1).clone(),
+                    px.pen.last["cvio"].clone(), z.grad.clone()))
+    (l1, x1, c1, v1, g1), (l0, x0, c0, v0, g0) = out
+    ex = torch.zeros(px.pen.model.m, dtype=torch.bool, device=dev)
+    for blk in ("p_fr", "q_fr", "p_to", "q_to", "angle", "thermal_fr", "thermal_to", "ref"):
+        o, k = px.pen.model.block(blk)
+        ex[o:o + k] = True
+    assert torch.equal(x1, x0) and torch.equal(c1[:, ex], c0[:, ex])
+    assert float((c1 - c0).abs().max()) <= 1e-13 * float(c0.abs().max())
+    assert float(((l1 - l0).abs() / l0.abs()).max()) <= 1e-12
+    assert torch.allclose(v1, v0, rtol=1e-12, atol=1e-15)
+    assert float((g1 - g0).abs().max()) <= 1e-6 * float(g0.abs().max())
+    px.close()
