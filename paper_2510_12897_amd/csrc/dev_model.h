@@ -22,26 +22,31 @@ enum TaskKind : int32_t {
     T_DEV = 6      // phase 1: 64 devices: their rows, gradient and objective partial
 };
 
-// Half-edge record: what the branch phase leaves for the bus phase, per
-// (replica, branch, side), side 0 at the from bus, 1 at the to bus.  For the
-// weighted flow-row Hessian W = sum_r -y_r hess F_r of the branch, with u the
-// side's own voltage magnitude:
+// What the bus phase sums per half-edge (branch, side; side 0 at the from
+// bus, 1 at the to bus).  For the weighted flow-row Hessian
+// W = sum_r -y_r hess F_r of the branch, with u the side's own voltage
+// magnitude:
 //   R_TT = d2W/dth2  (the bus's (va, va) term; the (va_f, va_t) entry is -R_TT)
 //   R_MA = d2W/(du dva_own)  (the (vm, va) term; the (vm_own, va_other) entry is -R_MA)
 //   R_MM = d2W/du2
 //   R_UW = d2W/(dvm_f dvm_t)
 //   R_P, R_Q = the arc's p and q (its balance-row terms)
-// The J^T v phase uses the first two fields: the side's va and vm terms.
 enum RecField : int32_t { R_TT = 0, R_MA, R_MM, R_UW, R_P, R_Q, kRec };
-// Records are stored back to back, 48 bytes apart (16-byte aligned: three
-// 16-byte loads fetch one).  Padding them to 64-byte sectors was measured
-// slower, with the same three loads per lane (4 % on the 64-scenario batch)
-// and with each record fetched by four cooperating lanes: the extra bytes
-// written cost more than the aligned reads save.
-constexpr int kRecStride = kRec;
-// A set without the Hessian needs only the arc values of each half-edge:
-// records [P, Q], 16 bytes apart, in the same per-side arrays.
-constexpr int kRecPQ = 2;
+// What the branch phase leaves for it, one record per (replica, branch): P,
+// Q, MA, MM of the from side, TT, UW, and MA, MM, P, Q of the to side, so
+// that each side's six values are 48 contiguous bytes at a 16-byte address
+// (the rectangular form: P, Q, Bs, D, unused, A, Bs, D, P, Q).  A set without
+// the Hessian leaves none: its bus phase reads p and q from x.
+// The branch phase is bound by the bytes it writes, the bus phase by its
+// gathers.  Two 48-byte records per branch, one a side: 48-period set 31.0 us,
+// 200-copy N-1 set 48.9, 64-scenario batch 128.2 (30.4, 47.8, 126.7 with
+// 16-byte stores); this one 29.4, 47.7, 122.9; one of 48 bytes with p and q
+// read from x 30.2, 49.3, 125.9 (two more gathers per half-edge).  Padding to
+// 64-byte sectors was slower (4 % on the batch, in the two-record form).
+constexpr int kRecStride = 10;
+// Doubles of scratch per (replica, branch): the J^T v phase needs 4, and
+// opf_eval_set_noalloc's documented size limit counts 12.
+constexpr int kRecRoom = 12;
 
 // Storage parameters, stored [kStorPar][S] (structure of arrays).
 enum StorPar : int32_t { SP_EMAX = 0, SP_CHMAX, SP_DISMAX, SP_RATING, SP_QMIN, SP_QMAX, SP_ETAC, SP_ETAD, SP_R,
@@ -103,8 +108,9 @@ struct DevModel {
     // self-resetting arrival ticket of single-launch models
     double* obj_part;         // [ngchunks * npg]
     int32_t* obj_ticket;      // [1], zero between launches
-    // half-edge records passed from the branch phase to the bus phase:
-    // side s, replica r, branch l at rec + ((s * nrep + r) * L + l) * kRecStride
+    // records passed from the branch phase to the bus phase: replica r,
+    // branch l at rec + (r * L + l) * kRecStride; the J^T v phase's, two
+    // doubles (va, vm terms) per side: rec + ((s * nrep + r) * L + l) * 2
     double* rec;
     // the wave-packed bus segments again, 2 int32 per lane (kind word,
     // index): the compact form the two-launch bus waves read

@@ -14,18 +14,19 @@
 //  phase 1, branch items (one lane per branch, branch order, so branch data,
 //    multipliers and arc variables are read coalesced; only the four bus
 //    voltages are gathered): the four flow rows, the angle row and the two
-//    thermal rows (c, J), the arc Hessian diagonals, and one 48-byte record
-//    per half-edge (the weighted second derivatives of the branch's flow
-//    rows and the arc's p, q), written contiguously in branch order;
+//    thermal rows (c, J), the arc Hessian diagonals, and with the Hessian one
+//    80-byte record (the weighted second derivatives of its flow rows that
+//    its two half-edges need and the arcs' p, q), written contiguously in
+//    branch order;
 //    generator items: the gradient, the pg Hessian diagonal, reference and
 //    ramp rows, and one objective partial per (chunk, replica);
 //  phase 2, bus items: waves of packed bus segments [head, half-edges,
 //    generators] (the host packs them so no segment straddles a wave; an
 //    8-byte descriptor per lane, and the head lane's per-bus row offsets,
 //    shared with its segment by shuffle, give every output position).  Each
-//    half-edge lane reads its record (one aligned 48-byte gather), stages it
-//    in LDS, and the
-//    head lane reduces its segment in order (a segmented reduction) into the
+//    half-edge lane reads its side's 48 bytes of the record (one aligned
+//    gather; p, q from x when there is no record), stages them in LDS, and
+//    the head lane reduces its segment in order (a segmented reduction) into the
 //    balance rows and the bus's Hessian diagonal, while the first half-edge
 //    of each neighbour group writes the group's off-diagonal Hessian
 //    entries (parallel branches summed); all of these sit in the bus's own
@@ -112,6 +113,19 @@ __device__ __forceinline__ void st_sel(T* base, uint32_t idx, T v) {
         st_keep(base, idx, v);
 }
 
+// Two neighbouring values in one 16-byte store; the address is a multiple of
+// 8 bytes only, which global memory takes.
+typedef double d2 __attribute__((ext_vector_type(2)));
+typedef double d2_at8 __attribute__((ext_vector_type(2), aligned(8)));
+template <bool KEEP = false>
+__device__ __forceinline__ void st_pair(double* base, uint32_t idx, d2 v) {
+    d2_at8* p = reinterpret_cast<d2_at8*>(reinterpret_cast<char*>(base) + (uint32_t)(idx * 8u));
+    if constexpr (KEEP)
+        *p = v;
+    else
+        __builtin_nontemporal_store((d2_at8)v, p);
+}
+
 __device__ __forceinline__ Coef load_coef(const DevModel& m, uint32_t l) {
     const int64_t L = m.L;
     const double* c = m.coef;
@@ -124,12 +138,9 @@ __device__ __forceinline__ Coef in_service(const Coef& k, const DevModel& m, int
     return m.outage[r] == l ? Coef{0, 0, 0, 0, 0, 0, 0, 0} : k;
 }
 
-// Half-edge records of one side (0: from bus, 1: to bus) and replica r:
-// one record per branch (48 bytes, or 16 without the Hessian), branches in
-// order; the two sides are separate arrays, so one wave writes each side as
-// one contiguous run.
-__device__ __forceinline__ double* rec_side(const DevModel& m, int32_t r, int32_t side) {
-    return m.rec + ((int64_t)side * m.nrep + r) * m.L * kRecStride;
+// The records of replica r, branches in order (RecSlot).
+__device__ __forceinline__ double* rec_of(const DevModel& m, int32_t r) {
+    return m.rec + (int64_t)r * m.L * kRecStride;
 }
 // The J^T v records: two doubles (va term, vm term) per branch and side.
 __device__ __forceinline__ double* jt_rec_side(const DevModel& m, int32_t r, int32_t side) {
@@ -140,24 +151,30 @@ __device__ __forceinline__ double* jt_rec_side(const DevModel& m, int32_t r, int
 // PER * nvalid doubles starting at dst[first]: staged through LDS, so every
 // store instruction of the wave covers consecutive addresses (a lane's own
 // values are PER doubles apart, which would touch PER times more cache
-// lines per instruction).  KEEP selects the cached store (scratch read by a
-// later launch).  Every lane of the workgroup must call it.
+// lines per instruction), 16 bytes a lane: half the store instructions, of
+// which the memory pipeline takes one per 40 clocks in a branch phase
+// (48-period set 30.3 -> 29.3 us and 64-scenario batch 126.7 -> 122.9 us
+// together with the shared record; 200-copy N-1 set 48.9 -> 47.8 us alone).
+// KEEP selects the cached store (scratch read by a later launch).  Every lane
+// of the workgroup must call it.
 template <int PER, bool KEEP = false>
 __device__ __forceinline__ void store_run(double* stage, double* dst, uint32_t first, uint32_t nvalid,
                                           const double (&v)[PER]) {
-    const uint32_t lane = threadIdx.x;
+    const uint32_t lane = threadIdx.x, n = PER * nvalid;
 #pragma unroll
     for (int k = 0; k < PER; k++) stage[PER * lane + k] = v[k];
     __syncthreads();
+    const d2* pair = reinterpret_cast<const d2*>(stage);
 #pragma unroll
-    for (int k = 0; k < PER; k++) {
-        const uint32_t e = k * kBlock + lane;
-        if (e < PER * nvalid) {
-            if constexpr (KEEP)
-                st_keep(dst, first + e, stage[e]);
-            else
-                st(dst, first + e, stage[e]);
-        }
+    for (int k = 0; k < (PER + 1) / 2; k++) {
+        const uint32_t e = k * kBlock + lane;  // pair of the run
+        if (2 * e + 1 < n) st_pair<KEEP>(dst, first + 2 * e, pair[e]);
+    }
+    if ((n & 1) && lane == 0) {
+        if constexpr (KEEP)
+            st_keep(dst, first + n - 1, stage[n - 1]);
+        else
+            st(dst, first + n - 1, stage[n - 1]);
     }
     __syncthreads();
 }
@@ -486,14 +503,9 @@ __device__ void branch_task(const DevModel& m, const EvalOut& o, int32_t chunk, 
             flow_jrow(f4, f_lo, v);
             store_run<5>(stage, o.J + m.j_qto + 5 * ob, 5 * l0, nvalid, v);
             if (act) {
-                // block offsets need not be even, so these pairs are stored
-                // as two 8-byte values
-                st(o.J + m.j_ang + 2 * ob, 2 * l, f_lo ? 1.0 : -1.0);
-                st(o.J + m.j_ang + 2 * ob, 2 * l + 1, f_lo ? -1.0 : 1.0);
-                st(o.J + m.j_thf + 2 * ob, 2 * l, 2.0 * pf);
-                st(o.J + m.j_thf + 2 * ob, 2 * l + 1, 2.0 * qf);
-                st(o.J + m.j_tht + 2 * ob, 2 * l, 2.0 * pt);
-                st(o.J + m.j_tht + 2 * ob, 2 * l + 1, 2.0 * qt);
+                st_pair(o.J + m.j_ang + 2 * ob, 2 * l, d2{f_lo ? 1.0 : -1.0, f_lo ? -1.0 : 1.0});
+                st_pair(o.J + m.j_thf + 2 * ob, 2 * l, d2{2.0 * pf, 2.0 * qf});
+                st_pair(o.J + m.j_tht + 2 * ob, 2 * l, d2{2.0 * pt, 2.0 * qt});
             }
         }
         if (wantH && act) {
@@ -503,19 +515,10 @@ __device__ void branch_task(const DevModel& m, const EvalOut& o, int32_t chunk, 
             st(o.H + m.h_q + oa + L, l, 2.0 * yt);
         }
         if (wantH && !SINGLE) {
-            // the half-edge records [TT, MA, MM, UW, P, Q] of each side
             const Hterms h = hess_terms(k, y1, y2, y3, y4, u, w, C, S);
             // d/dva_f = d/dth, d/dva_t = -d/dth
-            const double rf[kRecStride] = {h.Stt, h.Sut, h.Suu, h.Suw, pf, qf};
-            store_run<kRecStride, true>(stage, rec_side(m, r, 0), kRecStride * l0, nvalid, rf);
-            const double rt[kRecStride] = {h.Stt, -h.Swt, h.Sww, h.Suw, pt, qt};
-            store_run<kRecStride, true>(stage, rec_side(m, r, 1), kRecStride * l0, nvalid, rt);
-        } else if (wantC && !SINGLE) {
-            // no Hessian: compact records [P, Q] (the balance rows need nothing else)
-            const double rf[kRecPQ] = {pf, qf};
-            store_run<kRecPQ, true>(stage, rec_side(m, r, 0), kRecPQ * l0, nvalid, rf);
-            const double rt[kRecPQ] = {pt, qt};
-            store_run<kRecPQ, true>(stage, rec_side(m, r, 1), kRecPQ * l0, nvalid, rt);
+            const double rec[kRecStride] = {pf, qf, h.Sut, h.Suu, h.Stt, h.Suw, -h.Swt, h.Sww, pt, qt};
+            store_run<kRecStride, true>(stage, rec_of(m, r), kRecStride * l0, nvalid, rec);
         }
     }
     if (o.g && act) {
@@ -621,16 +624,8 @@ __device__ void rbranch_task(const DevModel& m, const EvalOut& o, int32_t chunk,
         }
         if (wantH && !SINGLE) {
             const RW w = rect_w(k, t5, t6, y1, y2, y3, y4, y5, y6);
-            double rf[kRec], rt[kRec];
-            rect_record(w, 0, pf, qf, rf);
-            rect_record(w, 1, pt, qt, rt);
-            store_run<kRecStride, true>(stage, rec_side(m, r, 0), kRecStride * l0, nvalid, rf);
-            store_run<kRecStride, true>(stage, rec_side(m, r, 1), kRecStride * l0, nvalid, rt);
-        } else if (wantC && !SINGLE) {
-            const double rf[kRecPQ] = {pf, qf};
-            store_run<kRecPQ, true>(stage, rec_side(m, r, 0), kRecPQ * l0, nvalid, rf);
-            const double rt[kRecPQ] = {pt, qt};
-            store_run<kRecPQ, true>(stage, rec_side(m, r, 1), kRecPQ * l0, nvalid, rt);
+            const double rec[kRecStride] = {pf, qf, w.B, 2.0 * w.al, 0.0, w.A, -w.B, 2.0 * w.be, pt, qt};
+            store_run<kRecStride, true>(stage, rec_of(m, r), kRecStride * l0, nvalid, rec);
         }
     }
     if (o.g && act) {
@@ -805,7 +800,7 @@ __device__ void wave_task(const DevModel& m, const EvalOut& o, int32_t w, int32_
         // into a register another type's load is still filling would make
         // the wave wait for that load.
         double gs, bs, vm_i, vr_i, pd, qd, yp, yq, ymag, gp, gq;
-        double2 ra, rb, rc;
+        double2 ra, rb;
         HeIn e;
         RHeIn re;
         int32_t jrow, hva0, hvm0, nlo, nd;  // the head's per-bus offsets (compact slots)
@@ -842,14 +837,20 @@ __device__ void wave_task(const DevModel& m, const EvalOut& o, int32_t w, int32_
             else
                 half_edge_load(m, o, ref, side, side ? other : bus, side ? bus : other, r, e);
         } else if (type == SK_EDGE) {
-            const double2* rec = reinterpret_cast<const double2*>(rec_side(m, r, (int32_t)side));
             if (wantH) {
+                const double2* rec = reinterpret_cast<const double2*>(rec_of(m, r));
                 const uint32_t q = (kRecStride / 2) * ref;
-                ra = ld(rec, q);
-                rb = ld(rec, q + 1);
-                if (wantC) rc = ld(rec, q + 2);
-            } else if (wantC) {  // compact records [P, Q]
-                rc = ld(rec, ref);
+                ra = ld(rec, q + (side ? 3 : 1));
+                rb = ld(rec, q + 2);
+                if (wantC) {
+                    const double2 rc = ld(rec, q + 4 * side);
+                    gp = rc.x;
+                    gq = rc.y;
+                }
+            } else if (wantC) {
+                const uint32_t a = ref + (side ? (uint32_t)m.L : 0u);
+                gp = ld(o.x + m.x_p + 2 * (int64_t)m.L * r, a);
+                gq = ld(o.x + m.x_q + 2 * (int64_t)m.L * r, a);
             }
         } else if (EXT && type == SK_GEN && (kind & 4)) {
             // a storage unit: ps, qs (and for its (vm, vm) term the loss
@@ -899,14 +900,14 @@ __device__ void wave_task(const DevModel& m, const EvalOut& o, int32_t w, int32_
                 half_edge_record(m, o, e, ref, side, k, r, v);
         } else if (type == SK_EDGE) {
             if (wantH) {
-                v[R_TT] = ra.x;
-                v[R_MA] = ra.y;
-                v[R_MM] = rb.x;
+                v[R_MA] = ra.x;
+                v[R_MM] = ra.y;
+                v[R_TT] = RECT ? ra.y : rb.x;
                 v[R_UW] = rb.y;
             }
             if (wantC) {
-                v[R_P] = rc.x;
-                v[R_Q] = rc.y;
+                v[R_P] = gp;
+                v[R_Q] = gq;
             }
         } else if (EXT && type == SK_GEN && (kind & 4)) {  // storage: +ps, +qs
             if (wantC) {
@@ -1138,7 +1139,7 @@ __device__ void jt_wave_task(const DevModel& m, const EvalOut& o, int32_t w, int
 // bus: recomputed in a single launch, else read from the branch phase.
 template <bool SINGLE, bool RECT>
 __device__ __forceinline__ void big_record(const DevModel& m, const EvalOut& o, int32_t code, int32_t r,
-                                           const double* rec0, const double* rec1, double (&v)[kRec]) {
+                                           double (&v)[kRec]) {
     const uint32_t l = (uint32_t)(code >> 1), side = (code & 1) ? 0u : 1u;
     if (SINGLE) {
         for (int q = 0; q < kRec; q++) v[q] = 0.0;
@@ -1152,14 +1153,20 @@ __device__ __forceinline__ void big_record(const DevModel& m, const EvalOut& o, 
             half_edge_load(m, o, l, side, (uint32_t)ld(m.f_bus, l), (uint32_t)ld(m.t_bus, l), r, e);
             half_edge_record(m, o, e, l, side, k, r, v);
         }
-    } else if (o.H) {
-        const double* rec = (side == 0 ? rec0 : rec1) + (int64_t)l * kRecStride;
-        for (int q = 0; q < kRec; q++) v[q] = rec[q];
-    } else {  // compact records [P, Q]
-        const double* rec = (side == 0 ? rec0 : rec1) + (int64_t)l * kRecPQ;
+    } else {
         for (int q = 0; q < kRec; q++) v[q] = 0.0;
-        v[R_P] = rec[0];
-        v[R_Q] = rec[1];
+        if (o.H) {
+            const double* rec = rec_of(m, r) + (int64_t)l * kRecStride;
+            v[R_MA] = rec[2 + 4 * side];
+            v[R_MM] = rec[3 + 4 * side];
+            v[R_TT] = RECT ? v[R_MM] : rec[4];
+            v[R_UW] = rec[5];
+        }
+        if (o.c) {
+            const int64_t a = l + (side ? m.L : 0) + 2 * (int64_t)m.L * r;
+            v[R_P] = o.x[m.x_p + a];
+            v[R_Q] = o.x[m.x_q + a];
+        }
     }
 }
 
@@ -1179,13 +1186,11 @@ __device__ void big_task(const DevModel& m, const EvalOut& o, int32_t idx, int32
         const double vm = x[m.x_vm + bi];             // rectangular: vi
         const double vr = RECT ? x[m.x_va + bi] : 0.0;
         const double v2 = RECT ? vr * vr + vm * vm : vm * vm;
-        const double* rec0 = rec_side(m, r, 0);
-        const double* rec1 = rec_side(m, r, 1);
         if (wantC || wantH) {
             double sp = 0.0, sq = 0.0, daa = 0.0, dma = 0.0, dmm = 0.0;
             for (int32_t q = threadIdx.x; q < deg; q += kBlock) {
                 double rec[kRec];
-                big_record<SINGLE, RECT>(m, o, m.he[e0 + q], r, rec0, rec1, rec);
+                big_record<SINGLE, RECT>(m, o, m.he[e0 + q], r, rec);
                 if (wantC) {
                     sp += rec[R_P];
                     sq += rec[R_Q];
@@ -1212,7 +1217,7 @@ __device__ void big_task(const DevModel& m, const EvalOut& o, int32_t idx, int32
                     double tt = 0.0, ma = 0.0, uw = 0.0;
                     for (int32_t q = e; q < e1 && m.he_grp[q] == grp; q++) {
                         double rec[kRec];
-                        big_record<SINGLE, RECT>(m, o, m.he[q], r, rec0, rec1, rec);
+                        big_record<SINGLE, RECT>(m, o, m.he[q], r, rec);
                         tt += rec[R_TT];
                         ma += rec[R_MA];
                         uw += rec[R_UW];
@@ -1782,7 +1787,7 @@ __device__ __forceinline__ void decode_phase2(const SetGrid& g, const DevModel& 
 
 template <int MODE, bool RECT, bool EXT>
 __global__ void __launch_bounds__(kBlock, 6) branch_kernel(DevModel m, EvalOut o, SetGrid g) {
-    __shared__ double stage[kRecStride * kBlock];
+    __shared__ __align__(16) double stage[kRecStride * kBlock];
     int32_t kind, idx, r;
     decode_phase1<EXT>(g, m, xcd_item(blockIdx.x, gridDim.x), kind, idx, r);
     run_phase1<MODE, RECT, EXT>(m, o, kind, idx, r, stage);
@@ -1796,7 +1801,7 @@ __global__ void __launch_bounds__(kBlock, 6) branch_kernel(DevModel m, EvalOut o
 // latency, not by the lines that neighbouring items share.
 template <bool RECT, bool EXT>
 __global__ void __launch_bounds__(kBlock) set_kernel_single(DevModel m, EvalOut o, SetGrid g) {
-    __shared__ double lds[kRecStride * kBlock];
+    __shared__ __align__(16) double lds[kRec * kBlock];
     int32_t b = blockIdx.x;
     if (b < g.n_branch) {
         if (RECT)
@@ -1833,7 +1838,7 @@ __global__ void __launch_bounds__(kBlock) set_kernel_single(DevModel m, EvalOut 
 
 template <int MODE, bool RECT, bool EXT>
 __global__ void __launch_bounds__(kBlock, 6) bus_kernel(DevModel m, EvalOut o, SetGrid g) {
-    __shared__ double lds[kRecStride * kBlock];
+    __shared__ __align__(16) double lds[kRec * kBlock];
     int32_t kind, idx, r;
     decode_phase2(g, m, xcd_item(blockIdx.x, gridDim.x), kind, idx, r);
     run_phase2<MODE, RECT, EXT>(m, o, kind, idx, r, lds);
@@ -1888,7 +1893,7 @@ __device__ __forceinline__ void xcd_stride(int32_t n, int32_t& first, int32_t& s
 
 template <int MODE, bool RECT, bool EXT>
 __global__ void __launch_bounds__(kBlock) batch_branch_kernel(BatchArgs a) {
-    __shared__ double stage[kRecStride * kBlock];
+    __shared__ __align__(16) double stage[kRecStride * kBlock];
     int32_t it, step, end;
     xcd_stride(a.n_items, it, step, end);
     for (; it < end; it += step) {
@@ -1900,7 +1905,7 @@ __global__ void __launch_bounds__(kBlock) batch_branch_kernel(BatchArgs a) {
 
 template <int MODE, bool RECT, bool EXT>
 __global__ void __launch_bounds__(kBlock) batch_bus_kernel(BatchArgs a) {
-    __shared__ double lds[kRecStride * kBlock];
+    __shared__ __align__(16) double lds[kRec * kBlock];
     int32_t it, step, end;
     xcd_stride(a.n_items, it, step, end);
     for (; it < end; it += step) {
@@ -1913,7 +1918,7 @@ __global__ void __launch_bounds__(kBlock) batch_bus_kernel(BatchArgs a) {
 
 template <int MODE, bool RECT, bool EXT>
 __global__ void __launch_bounds__(kBlock) batch_branch_flat(BatchArgs a) {
-    __shared__ double stage[kRecStride * kBlock];
+    __shared__ __align__(16) double stage[kRecStride * kBlock];
     const int32_t it = xcd_item(blockIdx.x, gridDim.x);
     if (it >= a.n_items) return;
     const BatchItem w = a.items[it];
@@ -1927,7 +1932,7 @@ __global__ void __launch_bounds__(kBlock) batch_branch_flat(BatchArgs a) {
 
 template <int MODE, bool RECT, bool EXT>
 __global__ void __launch_bounds__(kBlock, 5) batch_bus_flat(BatchArgs a) {
-    __shared__ double lds[kRecStride * kBlock];
+    __shared__ __align__(16) double lds[kRec * kBlock];
     const int32_t it = xcd_item(blockIdx.x, gridDim.x);
     if (it >= a.n_items) return;
     const BatchItem w = a.items[it];
@@ -1944,7 +1949,7 @@ __global__ void __launch_bounds__(kBlock, 5) batch_bus_flat(BatchArgs a) {
 // task in its one-launch form.
 template <bool RECT, bool EXT>
 __global__ void __launch_bounds__(kBlock) batch_single_flat(BatchArgs a) {
-    __shared__ double lds[kRecStride * kBlock];
+    __shared__ __align__(16) double lds[kRec * kBlock];
     const int32_t it = blockIdx.x;
     if (it >= a.n_items) return;
     const BatchItem w = a.items[it];
@@ -2070,7 +2075,7 @@ void* batch_kernel_fn(int phase, int mode, bool flat, bool rect, bool ext) {
 
 size_t scratch_bytes(const DevModel& m) {
     const size_t parts = ((sizeof(double) * (size_t)obj_slots(m)) + 255) & ~size_t(255);
-    return parts + 256 + sizeof(double) * (size_t)kRecStride * 2 * m.nrep * m.L;
+    return parts + 256 + sizeof(double) * (size_t)kRecRoom * m.nrep * m.L;
 }
 
 }  // namespace opf

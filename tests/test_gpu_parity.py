@@ -324,3 +324,35 @@ def test_torch_caching_allocator_hook():
     assert not live
     model2.close()
     ref_model.close()
+
+
+@pytest.mark.parametrize("L", [63, 64, 65, 127, 129])
+@pytest.mark.parametrize("form", ["polar", "rect"])
+@pytest.mark.parametrize("limit", [0, 4096])
+def test_outputs_at_any_8_byte_address(L, form, limit):
+    """Whole and partial branch chunks with the outputs 8 bytes off a 16-byte
+    address and on it: the same bits either way, with and without the Hessian
+    (its records), nothing written outside, and the two launch shapes agree."""
+    cs = synth.network(40, L, 9, 5, variant=True)
+    opf.set_single_launch_limit(limit)
+    try:
+        m = opf.Model(cs, form=form)
+    finally:
+        opf.set_single_launch_limit(4096)
+    one = opf.Model(cs, form=form)
+    g = torch.Generator(device=DEV).manual_seed(L)
+    x = torch.rand(m.n, dtype=torch.float64, device=DEV, generator=g) + 0.5
+    y = torch.randn(m.m, dtype=torch.float64, device=DEV, generator=g)
+    sizes = dict(f=1, g=m.n, c=m.m, jvals=m.nnzj, hvals=m.nnzh)
+    names = ("f", "g", "c", "jvals", "hvals")
+    ref = dict(zip(names, one.eval_set(x, y, 0.7)))
+    for off in (0, 1):
+        for want in (names, ("f", "g", "c", "jvals"), ("c",)):
+            buf = {k: torch.full((sizes[k] + 4,), float("nan"), dtype=torch.float64, device=DEV) for k in want}
+            m.eval_set(x, y, 0.7, alloc=False, **{k: b[off:off + sizes[k]] for k, b in buf.items()})
+            torch.cuda.synchronize()
+            for k, b in buf.items():
+                assert torch.equal(b[off:off + sizes[k]], ref[k]), (k, off)
+                assert torch.isnan(b[:off]).all() and torch.isnan(b[off + sizes[k]:]).all(), (k, off)
+    m.close()
+    one.close()
