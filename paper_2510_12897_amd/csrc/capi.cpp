@@ -564,7 +564,13 @@ int opf_jtprod(opf_model m, const double* x, const double* v, double* out, void*
     if (!x || !v || !out) return set_err(OPF_E_ARG, "x, v and out must be non-NULL");
     DeviceGuard dg(m->device);
     if (dg.err != hipSuccess) return hip_err(dg.err, "hipSetDevice");
-    hipError_t e = opf::launch_jtprod(m->dm, x, v, out, static_cast<hipStream_t>(stream));
+    const opf::Layout& ly = m->hm.ly;
+    auto apart = [&](const double* p, int64_t n) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(out);
+        return a + sizeof(double) * (size_t)n <= b || b + sizeof(double) * (size_t)ly.n <= a;
+    };
+    hipError_t e = opf::launch_jtprod(m->dm, x, v, out, apart(x, ly.n) && apart(v, ly.m()),
+                                      static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_err(e, "jtprod kernel launch");
     return OPF_OK;
 }

@@ -15,8 +15,9 @@ SetGrid plan_set(const DevModel& m, const EvalOut& o, int32_t mode);
 // phase, then the bus phase.
 hipError_t launch_eval_set(const DevModel& m, const EvalOut& o, hipStream_t stream);
 
-// out = J(x)^T v on `stream`.
-hipError_t launch_jtprod(const DevModel& m, const double* x, const double* v, double* out, hipStream_t stream);
+// out = J(x)^T v on `stream`; apart: out overlaps neither x nor v.
+hipError_t launch_jtprod(const DevModel& m, const double* x, const double* v, double* out, bool apart,
+                         hipStream_t stream);
 
 // ---- batched evaluation: one kernel per phase over a list of work items
 // (persistent, or one workgroup per item).

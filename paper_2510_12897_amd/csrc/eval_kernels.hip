@@ -639,6 +639,7 @@ __device__ void rbranch_task(const DevModel& m, const EvalOut& o, int32_t chunk,
 // J^T v of the rectangular form, phase 1: the arc entries (as polar) and
 // each half-edge's (vr, vi) terms: the gradient of W = sum_r v_r c_r over
 // the branch's six voltage rows at the side's own bus.
+template <bool SINGLE>
 __device__ void rjt_branch_task(const DevModel& m, const EvalOut& o, int32_t chunk, int32_t r) {
     const uint32_t l = (uint32_t)(chunk * kBlock) + threadIdx.x;
     if (l >= (uint32_t)m.L) return;
@@ -667,6 +668,7 @@ __device__ void rjt_branch_task(const DevModel& m, const EvalOut& o, int32_t chu
     st(o.g + m.x_p + oa + L, l, v3 + bpt + 2.0 * pt * vtt);
     st(o.g + m.x_q + oa, l, v2 + bqf + 2.0 * qf * vtf);
     st(o.g + m.x_q + oa + L, l, v4 + bqt + 2.0 * qt * vtt);
+    if (SINGLE) return;
     const RW w = rect_w(k, t5, t6, v1, v2, v3, v4, v5, v6);
     const double CR = 0.0, SI = 0.0;
     const RTerm d = rterm(w.al, w.be, w.A, w.B, e, CR, SI, 0.0, 0.0);
@@ -674,8 +676,52 @@ __device__ void rjt_branch_task(const DevModel& m, const EvalOut& o, int32_t chu
     st_keep(reinterpret_cast<double2*>(jt_rec_side(m, r, 1)), l, make_double2(d.Drt, d.Djt));
 }
 
+// What one half-edge adds to its bus's J^T v entries (va and vm, rectangular
+// vr and vi), recomputed from x and v with the branch task's arithmetic (one
+// launch).  Loads first, arithmetic second, as half_edge_load / _record.
+struct JHeIn {
+    double v1, v2, v3, v4, v5, v6, t5, t6;
+    RVolt e;  // polar: vm_f, vm_t, va_f, va_t
+};
+template <bool RECT>
+__device__ __forceinline__ void jt_edge_load(const DevModel& m, const EvalOut& o, uint32_t l, uint32_t fb, uint32_t tb,
+                                             int32_t r, JHeIn& h) {
+    const int64_t L = m.L, N = m.N, ob = L * r, on = N * r;
+    h.v1 = ld(o.y + m.c_pfr + ob, l);
+    h.v2 = ld(o.y + m.c_qfr + ob, l);
+    h.v3 = ld(o.y + m.c_pto + ob, l);
+    h.v4 = ld(o.y + m.c_qto + ob, l);
+    h.v5 = ld(o.y + m.c_ang + ob, l);
+    if (RECT) {
+        h.v6 = ld(o.y + m.c_angl + ob, l);
+        h.t5 = ld(m.tan_lim, l);
+        h.t6 = ld(m.tan_lim + L, l);
+    }
+    const double* xr = o.x + (RECT ? m.x_va : m.x_vm) + on;
+    const double* xj = o.x + (RECT ? m.x_vm : m.x_va) + on;
+    h.e.rf = ld(xr, fb);
+    h.e.rt = ld(xr, tb);
+    h.e.jf = ld(xj, fb);
+    h.e.jt = ld(xj, tb);
+}
+template <bool RECT>
+__device__ __forceinline__ double2 jt_edge_terms(const DevModel& m, const JHeIn& h, uint32_t l, uint32_t side,
+                                                 const Coef& k0, int32_t r) {
+    const Coef k = in_service(k0, m, (int32_t)l, r);
+    if (RECT) {
+        const RW w = rect_w(k, h.t5, h.t6, h.v1, h.v2, h.v3, h.v4, h.v5, h.v6);
+        const RTerm d = rterm(w.al, w.be, w.A, w.B, h.e, 0.0, 0.0, 0.0, 0.0);
+        return side ? make_double2(d.Drt, d.Djt) : make_double2(d.Drf, d.Djf);
+    }
+    double S, C;
+    sincos(h.e.jf - h.e.jt, &S, &C);
+    const Jterms j = jt_terms(k, h.v1, h.v2, h.v3, h.v4, h.e.rf, h.e.rt, C, S);
+    return side ? make_double2(-j.Dt - h.v5, j.Dw) : make_double2(j.Dt + h.v5, j.Du);
+}
+
 // J^T v, phase 1: the arc entries p / q (owned here) and each half-edge's
-// va / vm terms for the bus side.
+// va / vm terms for the bus side (in one launch the bus items recompute them).
+template <bool SINGLE>
 __device__ void jt_branch_task(const DevModel& m, const EvalOut& o, int32_t chunk, int32_t r) {
     const uint32_t l = (uint32_t)(chunk * kBlock) + threadIdx.x;
     if (l >= (uint32_t)m.L) return;
@@ -704,6 +750,7 @@ __device__ void jt_branch_task(const DevModel& m, const EvalOut& o, int32_t chun
         st(o.g + m.x_p + oa + L, l, v3 + bpt + 2.0 * pt * vtt);
         st(o.g + m.x_q + oa, l, v2 + bqf + 2.0 * qf * vtf);
         st(o.g + m.x_q + oa + L, l, v4 + bqt + 2.0 * qt * vtt);
+        if (SINGLE) return;
         double S, C;
         sincos(th, &S, &C);
         const Jterms j = jt_terms(k, v1, v2, v3, v4, u, w, C, S);
@@ -1060,17 +1107,37 @@ __device__ void wave_task(const DevModel& m, const EvalOut& o, int32_t w, int32_
 #undef JP
 
 // J^T v, phase 2: va / vm (rectangular: vr / vi) entries of the packed buses.
-template <bool RECT = false, bool EXT = false>
+template <bool SINGLE, bool RECT = false, bool EXT = false>
 __device__ void jt_wave_task(const DevModel& m, const EvalOut& o, int32_t w, int32_t r, double* lds) {
     const int32_t lane = threadIdx.x;
     // the compact slot: lane type, side, segment length; the index is the
-    // bus (head) or the branch (half-edge)
-    const int2 sc = ld(reinterpret_cast<const int2*>(m.slots_c) + (size_t)w * kBlock, (uint32_t)lane);
-    const int32_t type = sc.x & 3;
-    const uint32_t side = (sc.x & 4) ? 0u : 1u;
-    const int32_t len = ((sc.x >> 8) & 63) + 1;
+    // bus (head) or the branch (half-edge).  One launch: the full slot, for
+    // the neighbour bus, and the lane's branch terms beside it.
+    Coef k{};
+    int32_t kind, len, head;
+    uint32_t bus, ref, other = 0;
+    if (SINGLE) {
+        const double2* kc = reinterpret_cast<const double2*>(m.slot_coef) + (size_t)w * kBlock * 4;
+        const double2 c01 = ld(kc, 4 * lane), c23 = ld(kc, 4 * lane + 1);
+        const double2 c45 = ld(kc, 4 * lane + 2), c67 = ld(kc, 4 * lane + 3);
+        k = Coef{c01.x, c01.y, c23.x, c23.y, c45.x, c45.y, c67.x, c67.y};
+        const Slot sl = load_slot(m, w);
+        kind = sl.kind;
+        len = (kind >> 8) & 0xff;
+        bus = (uint32_t)sl.bus;
+        ref = (uint32_t)sl.ref;
+        other = (uint32_t)sl.other;
+        head = sl.other & 63;
+    } else {
+        const int2 sc = ld(reinterpret_cast<const int2*>(m.slots_c) + (size_t)w * kBlock, (uint32_t)lane);
+        kind = sc.x;
+        len = ((kind >> 8) & 63) + 1;
+        bus = ref = (uint32_t)sc.y;
+        head = (kind >> 14) & 63;
+    }
+    const int32_t type = kind & 3;
+    const uint32_t side = (kind & 4) ? 0u : 1u;
     const int64_t N = m.N;
-    const uint32_t bus = (uint32_t)sc.y, ref = (uint32_t)sc.y;
     const double* x = o.x;
     const double* v = o.y;
     {  // replica r
@@ -1081,9 +1148,12 @@ __device__ void jt_wave_task(const DevModel& m, const EvalOut& o, int32_t w, int
         double2 t;
         double vm, vr, gs, bs, vp, vq, vg;
         int32_t q0, q1;
-        if (type == SK_EDGE) {
+        JHeIn h;
+        if (type == SK_EDGE && SINGLE) {
+            jt_edge_load<RECT>(m, o, ref, side ? other : bus, side ? bus : other, r, h);
+        } else if (type == SK_EDGE) {
             t = ld(reinterpret_cast<const double2*>(jt_rec_side(m, r, (int32_t)side)), ref);
-        } else if (EXT && type == SK_GEN && (sc.x & 4)) {
+        } else if (EXT && type == SK_GEN && (kind & 4)) {
             // a storage unit's loss rows: ps, qs, their multipliers, r, x
             // (in the registers of the head's loads)
             const int64_t S = m.S;
@@ -1107,8 +1177,9 @@ __device__ void jt_wave_task(const DevModel& m, const EvalOut& o, int32_t w, int
             q1 = ld(m.ref_ptr, bus + 1);
         }
         double vm_h = 0.0;
-        if (EXT && m.S > 0) vm_h = __shfl(vm, (sc.x >> 14) & 63, kBlock);
-        const bool stor = EXT && type == SK_GEN && (sc.x & 4);
+        if (EXT && m.S > 0) vm_h = __shfl(vm, head, kBlock);
+        const bool stor = EXT && type == SK_GEN && (kind & 4);
+        if (SINGLE && type == SK_EDGE) t = jt_edge_terms<RECT>(m, h, ref, side, k, r);
         lds[0 * kBlock + lane] = type == SK_EDGE ? t.x : 0.0;
         lds[1 * kBlock + lane] = type == SK_EDGE ? t.y : stor ? jt_stor_vm(vr, vg, vm_h, vp, vq, gs, bs) : 0.0;
         __syncthreads();
@@ -1323,7 +1394,7 @@ __device__ void big_task(const DevModel& m, const EvalOut& o, int32_t idx, int32
     }
 }
 
-template <bool RECT = false, bool EXT = false>
+template <bool SINGLE, bool RECT = false, bool EXT = false>
 __device__ void jt_big_task(const DevModel& m, const EvalOut& o, int32_t idx, int32_t r) {
     const int32_t b = m.big_bus[idx];
     const int32_t e0 = m.adj_ptr[b], deg = m.adj_ptr[b + 1] - e0;
@@ -1336,9 +1407,18 @@ __device__ void jt_big_task(const DevModel& m, const EvalOut& o, int32_t idx, in
         double sa = 0.0, sm = 0.0;
         for (int32_t q = threadIdx.x; q < deg; q += kBlock) {
             const int32_t code = m.he[e0 + q];
-            const double* rec = ((code & 1) ? rec0 : rec1) + (int64_t)(code >> 1) * 2;
-            sa += rec[0];
-            sm += rec[1];
+            double2 t;
+            if (SINGLE) {
+                const uint32_t l = (uint32_t)(code >> 1);
+                JHeIn h;
+                jt_edge_load<RECT>(m, o, l, (uint32_t)ld(m.f_bus, l), (uint32_t)ld(m.t_bus, l), r, h);
+                t = jt_edge_terms<RECT>(m, h, l, (code & 1) ? 0u : 1u, load_coef(m, l), r);
+            } else {
+                const double* rec = ((code & 1) ? rec0 : rec1) + (int64_t)(code >> 1) * 2;
+                t = make_double2(rec[0], rec[1]);
+            }
+            sa += t.x;
+            sm += t.y;
         }
         sa = wave_sum(sa);
         sm = wave_sum(sm);
@@ -1687,7 +1767,8 @@ __device__ void jt_dev_task(const DevModel& m, const EvalOut& o, int32_t chunk, 
 // pointer (more than doubling the branch task's registers).
 // RECT selects the rectangular form's tasks (every kernel is instantiated
 // for both forms; a launch takes the model's).
-template <int MODE, bool RECT, bool EXT>
+// SINGLE: the one-launch form of J^T v (callback sets: set_kernel_single).
+template <int MODE, bool RECT, bool EXT, bool SINGLE = false>
 __device__ __forceinline__ void run_phase1(const DevModel& m, const EvalOut& o, int32_t kind, int32_t idx, int32_t r,
                                            double* stage) {
     if (MODE == 0) {
@@ -1707,15 +1788,15 @@ __device__ __forceinline__ void run_phase1(const DevModel& m, const EvalOut& o, 
         else if (EXT && kind == T_DEV)
             jt_dev_task(m, o, idx, r);
         else if (RECT)
-            rjt_branch_task(m, o, idx, r);
+            rjt_branch_task<SINGLE>(m, o, idx, r);
         else
-            jt_branch_task(m, o, idx, r);
+            jt_branch_task<SINGLE>(m, o, idx, r);
     } else if (kind == T_BRANCH) {
         flows_task(m, o, idx, r);
     }
 }
 
-template <int MODE, bool RECT, bool EXT>
+template <int MODE, bool RECT, bool EXT, bool SINGLE = false>
 __device__ __forceinline__ void run_phase2(const DevModel& m, const EvalOut& o, int32_t kind, int32_t idx, int32_t r,
                                            double* lds) {
     if (MODE == 0) {
@@ -1726,8 +1807,8 @@ __device__ __forceinline__ void run_phase2(const DevModel& m, const EvalOut& o, 
         }
     } else {
         switch (kind) {
-        case T_BIG: jt_big_task<RECT, EXT>(m, o, idx, r); break;
-        case T_WAVE: jt_wave_task<RECT, EXT>(m, o, idx, r, lds); break;
+        case T_BIG: jt_big_task<SINGLE, RECT, EXT>(m, o, idx, r); break;
+        case T_WAVE: jt_wave_task<SINGLE, RECT, EXT>(m, o, idx, r, lds); break;
         default: jt_gen_task(m, o, idx, r); break;
         }
     }
@@ -1842,6 +1923,23 @@ __global__ void __launch_bounds__(kBlock, 6) bus_kernel(DevModel m, EvalOut o, S
     int32_t kind, idx, r;
     decode_phase2(g, m, xcd_item(blockIdx.x, gridDim.x), kind, idx, r);
     run_phase2<MODE, RECT, EXT>(m, o, kind, idx, r, lds);
+}
+
+// The single launch of a small model's J^T v: the items of both phases, dealt
+// round-robin as in set_kernel_single; bus items recompute their half-edge
+// terms, so no item reads what another writes.
+template <bool RECT, bool EXT>
+__global__ void __launch_bounds__(kBlock) jt_kernel_single(DevModel m, EvalOut o, SetGrid g) {
+    __shared__ __align__(16) double lds[2 * kBlock];
+    const int32_t b = blockIdx.x, n1 = g.n_branch + g.n_gen1 + g.n_stor + g.n_dev;
+    int32_t kind, idx, r;
+    if (b < n1) {
+        decode_phase1<EXT>(g, m, b, kind, idx, r);
+        run_phase1<1, RECT, EXT, true>(m, o, kind, idx, r, lds);
+    } else {
+        decode_phase2(g, m, b - n1, kind, idx, r);
+        run_phase2<1, RECT, EXT, true>(m, o, kind, idx, r, lds);
+    }
 }
 
 // Occupancy hints (second launch-bounds argument: waves per SIMD) are the
@@ -2020,9 +2118,19 @@ hipError_t launch_eval_set(const DevModel& m, const EvalOut& o_in, hipStream_t s
     return m.rect ? launch_set_form<true, false>(m, o, stream) : launch_set_form<false, false>(m, o, stream);
 }
 
+constexpr int32_t kJtSingleItems = 2048;
 template <bool RECT, bool EXT>
 hipError_t launch_jt_form(const DevModel& m, const EvalOut& o, hipStream_t stream) {
     const SetGrid g = plan_set(m, o, 1);
+    // One launch for a set's one-launch models up to eight waves per compute
+    // unit, where the launch and the records' round trip are what it saves
+    // (300 buses 5.8 -> 3.7 us, 10,000 buses 6.6 -> 5.8; rectangular 20,000
+    // buses, 1,700 items, 9.1 -> 8.3, but 30,000, 2,500 items, 11.2 -> 11.8).
+    const int32_t n = g.phase1() + g.phase2();
+    if (o.single && n <= kJtSingleItems) {
+        if (n > 0) hipLaunchKernelGGL((jt_kernel_single<RECT, EXT>), dim3(n), dim3(kBlock), 0, stream, m, o, g);
+        return hipGetLastError();
+    }
     if (g.phase1() > 0)
         hipLaunchKernelGGL((branch_kernel<1, RECT, EXT>), dim3(g.phase1()), dim3(kBlock), 0, stream, m, o, g);
     if (g.phase2() > 0)
@@ -2030,11 +2138,15 @@ hipError_t launch_jt_form(const DevModel& m, const EvalOut& o, hipStream_t strea
     return hipGetLastError();
 }
 
-hipError_t launch_jtprod(const DevModel& m, const double* x, const double* v, double* out, hipStream_t stream) {
+hipError_t launch_jtprod(const DevModel& m, const double* x, const double* v, double* out, bool apart,
+                         hipStream_t stream) {
     EvalOut o{};
     o.x = x;
     o.y = v;
     o.g = out;
+    // out over an input takes two launches: there every neighbour's value is
+    // read before the bus items write
+    o.single = m.single && apart;
     if (has_ext(m))
         return m.rect ? launch_jt_form<true, true>(m, o, stream) : launch_jt_form<false, true>(m, o, stream);
     return m.rect ? launch_jt_form<true, false>(m, o, stream) : launch_jt_form<false, false>(m, o, stream);

@@ -356,3 +356,40 @@ def test_outputs_at_any_8_byte_address(L, form, limit):
                 assert torch.isnan(b[:off]).all() and torch.isnan(b[off + sizes[k]:]).all(), (k, off)
     m.close()
     one.close()
+
+
+def _jt_cases():
+    yield from CASES
+    cs = synth.network(60, 85, 20, 13, variant=True)
+    pd_t, qd_t = synth.mp_loads(cs, 3, 2)
+    yield "storage", cs, dict(n_periods=3, pd_t=pd_t, qd_t=qd_t, ramp_ratio=0.2, storage=synth.storage(cs, 14),
+                              stor_dt=0.5, stor_comp=True, devices=synth.devices(cs, 30, 15))
+
+
+@pytest.mark.parametrize("name,cs,opts", list(_jt_cases()), ids=[c[0] for c in _jt_cases()])
+@pytest.mark.parametrize("form", ["polar", "rect"])
+def test_jtprod_launch_shapes_agree_and_take_an_output_over_an_input(name, cs, opts, form):
+    """J^T v in one launch and in two gives the same bits; without storage
+    units an output that lies over x has the result of one apart from it."""
+    try:
+        one = opf.Model(cs, form=form, **opts)
+    except opf.OPFError:
+        assert form == "rect"
+        pytest.skip("not a case of the rectangular form")
+    opf.set_single_launch_limit(0)
+    try:
+        two = opf.Model(cs, form=form, **opts)
+    finally:
+        opf.set_single_launch_limit(4096)
+    assert one.launch_shape()[0] == 1 and two.launch_shape()[0] == 2
+    g = torch.Generator(device=DEV).manual_seed(5)
+    x = torch.rand(one.n, dtype=torch.float64, device=DEV, generator=g) + 0.5
+    v = torch.randn(one.m, dtype=torch.float64, device=DEV, generator=g)
+    want = two.jtprod(x, v)
+    assert torch.equal(one.jtprod(x, v), want)
+    assert torch.equal(one.jtprod(x.clone(), v), want)
+    if "storage" not in opts:  # the storage items of the first launch write what the second one reads
+        over = x.clone()
+        assert torch.equal(one.jtprod(over, v, over), want)
+    one.close()
+    two.close()
