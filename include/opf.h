@@ -358,10 +358,21 @@ int opf_batch_jtprod(opf_batch batch, const double *X, const double *V, double *
  * OPF_E_STATE if the batch was created without per-instance loads. */
 int opf_batch_set_loads(opf_batch batch, const double *pd, const double *qd, void *stream);
 
+/* opf_batch_set_loads from rows that lie apart, in one launch: the loads'
+ * values in order, row of them together, the rows' starts stride apart in pd
+ * and in qd (on the batch's device). */
+int opf_batch_set_load_rows(opf_batch batch, const double *pd, const double *qd, int64_t row, int64_t stride,
+                            void *stream);
+
 /* Overwrite the arc variables p, q of every instance in X by the branch
  * flows F(vm, va) at X's voltages (so every flow-definition row of c(X) is
  * zero).  One launch. */
 int opf_batch_flows(opf_batch batch, double *X, void *stream);
+
+/* OUT = X with the arc variables so overwritten, in one launch; OUT is X
+ * itself or apart from it.  Static polar models with branches only
+ * (OPF_E_ARG otherwise). */
+int opf_batch_flows_to(opf_batch batch, const double *X, double *OUT, void *stream);
 
 /* ------------------------------------------------ learned warm-start proxy */
 /* Kernels of a multilayer perceptron that maps loads to (vm, va, pg, qg),

@@ -49,6 +49,7 @@ struct opf_batch_s {
     int32_t n_cu = 256;
     bool rect = false;               // every model is of the rectangular form (else all polar)
     bool ext = false;                // some model has storage units or devices
+    bool flat = true;                // every model is static, with branches: x ends with its arcs
 };
 
 namespace {
@@ -158,6 +159,10 @@ int opf_batch_create(const opf_model* models, int32_t n_models, const int32_t* i
         b = new opf_batch_s();
         b->device = dev;
         b->rect = models[0]->hm.ly.rect != 0;
+        for (int32_t k = 0; k < n_models; k++) {
+            const opf::Layout& ly = models[k]->hm.ly;
+            if (ly.nrep != 1 || ly.L < 1 || ly.x_q != ly.x_p + 2 * ly.L || ly.n != ly.x_q + 2 * ly.L) b->flat = false;
+        }
         for (int32_t k = 0; k < n_models; k++)
             if (models[k]->hm.ly.S > 0 || models[k]->hm.ly.D > 0) b->ext = true;
         b->alloc = current_allocator();
@@ -339,6 +344,33 @@ int opf_batch_set_loads(opf_batch b, const double* pd, const double* qd, void* s
     if (e == hipSuccess) e = hipMemcpyAsync(b->qd_all, qd, bytes, hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) return hip_err(e, "load copy");
     return OPF_OK;
+}
+
+int opf_batch_set_load_rows(opf_batch b, const double* pd, const double* qd, int64_t row, int64_t stride,
+                            void* stream) {
+    if (!valid(b)) return set_err(OPF_E_STATE, "invalid or destroyed batch handle");
+    if (!b->pd_all) return set_err(OPF_E_STATE, "the batch was created without per-instance loads");
+    if (!pd || !qd) return set_err(OPF_E_ARG, "pd and qd must be non-NULL");
+    if (row < 1 || stride < 0 || b->n_loads % row) return set_err(OPF_E_ARG, "rows of %lld values do not make up the loads", (long long)row);
+    DeviceGuard dg(b->device);
+    if (dg.err != hipSuccess) return hip_err(dg.err, "hipSetDevice");
+    const hipError_t e = opf::launch_load_rows(pd, qd, b->n_loads, row, stride, b->pd_all, b->qd_all,
+                                               static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return hip_err(e, "load rows launch");
+    return OPF_OK;
+}
+
+int opf_batch_flows_to(opf_batch b, const double* X, double* OUT, void* stream) {
+    if (!valid(b)) return set_err(OPF_E_STATE, "invalid or destroyed batch handle");
+    if (!X || !OUT) return set_err(OPF_E_ARG, "X and OUT must be non-NULL");
+    if (b->rect || !b->flat) return set_err(OPF_E_ARG, "opf_batch_flows_to takes static polar models only");
+    DeviceGuard dg(b->device);
+    if (dg.err != hipSuccess) return hip_err(dg.err, "hipSetDevice");
+    opf::BatchArgs a{};
+    a.X = X;
+    a.G = OUT;
+    a.mode = 2;
+    return launch(b, a, static_cast<hipStream_t>(stream));
 }
 
 int opf_batch_flows(opf_batch b, double* X, void* stream) {

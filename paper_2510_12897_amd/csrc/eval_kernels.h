@@ -39,8 +39,12 @@ struct BatchArgs {
     const double* sigma;
     double *F, *G, *C, *J, *H;
     int32_t mode;            // 0 = callback set, 1 = J^T v (Y holds V, G holds OUT),
-                             // 2 = arc flows (G is the X written in place)
+                             // 2 = arc flows into G (X itself, or a copy of a static X)
 };
+
+// pd_all, qd_all [n] from rows of row values, stride apart, of pd and qd.
+hipError_t launch_load_rows(const double* pd, const double* qd, int64_t n, int64_t row, int64_t stride, double* pd_all,
+                            double* qd_all, hipStream_t stream);
 
 // Scratch bytes a model needs per evaluation stream: objective partials,
 // then the half-edge records (kRec doubles per replica, branch, side).

@@ -140,7 +140,9 @@ def lib():
         "opf_batch_eval": ([_vp] + [_vp] * 8 + [_vp], ctypes.c_int),
         "opf_batch_jtprod": ([_vp, _vp, _vp, _vp, _vp], ctypes.c_int),
         "opf_batch_set_loads": ([_vp, _vp, _vp, _vp], ctypes.c_int),
+        "opf_batch_set_load_rows": ([_vp, _vp, _vp, ctypes.c_int64, ctypes.c_int64, _vp], ctypes.c_int),
         "opf_batch_flows": ([_vp, _vp, _vp], ctypes.c_int),
+        "opf_batch_flows_to": ([_vp, _vp, _vp, _vp], ctypes.c_int),
         "prox_gemm_bf16": ([ctypes.c_int, _vp, ctypes.c_int, _vp, ctypes.c_int, _vp, ctypes.c_int, ctypes.c_int,
                             ctypes.c_int, ctypes.c_int, _vp, _vp, ctypes.c_int, _vp], ctypes.c_int),
         "prox_gemm_bf16_splitk": ([ctypes.c_int, _vp, ctypes.c_int, _vp, ctypes.c_int, _vp, ctypes.c_int,
@@ -533,6 +535,7 @@ class Batch:
             pd = np.ascontiguousarray(inst_pd, dtype=np.float64).reshape(-1)
             qd = np.ascontiguousarray(inst_qd, dtype=np.float64).reshape(-1)
             self._keep += [pd, qd]
+        self.n_loads = 0 if pd is None else int(pd.size)
         h = _vp()
         _check(lib().opf_batch_create(arr, len(self.models), im.ctypes.data,
                                       pd.ctypes.data if pd is not None else None,
@@ -597,6 +600,28 @@ class Batch:
         torch = _torch()
         _check(lib().opf_batch_set_loads(self._h, _ptr(pd, None, torch.float64, "pd"),
                                          _ptr(qd, None, torch.float64, "qd"), _stream()))
+
+    def set_load_rows(self, pd, qd):
+        """set_loads from 2-D tensors whose rows may lie apart (slices of a
+        wider one).  False, with nothing done, where set_loads has to copy:
+        other strides, types, devices or sizes."""
+        torch = _torch()
+        for t in (pd, qd):
+            if not (t.is_cuda and t.dtype == torch.float64 and t.dim() == 2 and t.stride(1) == 1
+                    and t.device.index == self.device and not t.is_neg()):
+                return False
+        rows, row = pd.shape
+        if qd.shape != pd.shape or qd.stride(0) != pd.stride(0) or rows * row != self.n_loads or row == 0:
+            return False
+        _check(lib().opf_batch_set_load_rows(self._h, pd.data_ptr(), qd.data_ptr(), row, pd.stride(0), _stream()))
+        return True
+
+    def flows_to(self, X, OUT):
+        """OUT = X with the arc variables overwritten by the branch flows at
+        X's voltages (static polar models with branches)."""
+        d = _torch().float64
+        _check(lib().opf_batch_flows_to(self._h, _ptr(X, self.n, d, "X"), _ptr(OUT, self.n, d, "OUT"), _stream()))
+        return OUT
 
     def flows(self, X):
         """Overwrite the arc variables of X (in place) by the branch flows at

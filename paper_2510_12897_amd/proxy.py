@@ -324,8 +324,11 @@ def _make_penalty_function():
     class F(torch.autograd.Function):
         @staticmethod
         def forward(ctx, X, pen):
-            Xf = X.detach().clone()
-            pen.batch.flows(Xf)
+            Xf = X.detach()
+            if pen.L > 0 and Xf.is_contiguous():
+                Xf = pen.batch.flows_to(Xf, torch.empty_like(Xf))
+            else:
+                Xf = pen.batch.flows(Xf.clone())
             B, m = pen.B, pen.model.m
             dev = X.device
             Fo = torch.empty(B, dtype=torch.float64, device=dev)
@@ -479,7 +482,8 @@ class Penalty:
 
     def set_loads(self, pd, qd):
         """pd, qd: float64 device tensors [B, N]."""
-        self.batch.set_loads(pd.contiguous().view(-1), qd.contiguous().view(-1))
+        if not self.batch.set_load_rows(pd, qd):
+            self.batch.set_loads(pd.contiguous().view(-1), qd.contiguous().view(-1))
 
     def __call__(self, X):
         """Per-instance loss [B] of X [B, n] (FP64; its p, q are ignored)."""

@@ -260,3 +260,66 @@ def test_batch_instances_match_oracle():
     batch.close()
     for m in models:
         m.close()
+
+
+@pytest.mark.parametrize("N,L,G", [(3, 3, 1), (30, 29, 7), (70, 95, 40)])
+def test_flows_into_another_array(N, L, G):
+    """flows_to is a copy of X with flows in place, bit for bit: fewer branches
+    than free entries per chunk and more, one instance and several."""
+    cs = synth.network(N, L, G, 6)
+    m = opf.Model(cs)
+    g = torch.Generator(device=DEV).manual_seed(N)
+    for B in (1, 3):
+        b = opf.Batch([m], np.zeros(B, np.int32))
+        X = torch.rand(B * m.n, dtype=torch.float64, device=DEV, generator=g) + 0.5
+        keep, OUT = X.clone(), torch.full_like(X, float("nan"))
+        assert b.flows_to(X, OUT) is OUT
+        assert torch.equal(X, keep)
+        assert torch.equal(OUT, b.flows(X.clone()))
+        assert torch.equal(b.flows_to(keep, keep), OUT)
+        b.close()
+    m.close()
+    for opts in (dict(form="rect"), dict(n_periods=2, ramp_ratio=0.3)):
+        m = opf.Model(cs, **opts)
+        b = opf.Batch([m], np.zeros(1, np.int32))
+        X = torch.ones(m.n, dtype=torch.float64, device=DEV)
+        with pytest.raises(opf.OPFError, match="static polar"):
+            b.flows_to(X, X.clone())
+        b.close()
+        m.close()
+
+
+def test_loads_from_rows():
+    """set_load_rows takes every layout with dense rows on the batch's device
+    (slices, expanded rows, one column) and leaves the others to set_loads."""
+    N, B = 9, 4
+    cs = synth.network(N, 12, 3, 6)
+    m = opf.Model(cs)
+    b = opf.Batch([m], np.zeros(B, np.int32), np.tile(cs["pd"], B), np.tile(cs["qd"], B))
+    g = torch.Generator(device=DEV).manual_seed(1)
+    X = torch.rand(B * m.n, dtype=torch.float64, device=DEV, generator=g) + 0.5
+    wide = torch.randn(B, 2 * N + 3, dtype=torch.float64, device=DEV, generator=g)
+
+    def rows(pd, qd, taken):
+        ref, got = (torch.empty(b.m, dtype=torch.float64, device=DEV) for _ in range(2))
+        b.set_loads(pd.contiguous().view(-1), qd.contiguous().view(-1))
+        b.eval(X, C=ref)
+        b.set_loads(torch.zeros(B * N, dtype=torch.float64, device=DEV), torch.zeros(B * N, dtype=torch.float64, device=DEV))
+        assert b.set_load_rows(pd, qd) is taken
+        if taken:
+            b.eval(X, C=got)
+            assert torch.equal(got, ref)
+
+    rows(wide[:, :N], wide[:, N:2 * N], True)
+    rows(wide[:, :N].contiguous(), wide[:, N:2 * N].contiguous(), True)
+    rows(wide[:1, :N].expand(B, N), wide[1:2, 3:3 + N].expand(B, N), True)
+    rows(wide[:, :N], wide[:, N:2 * N].contiguous(), False)
+    rows(wide[:, :2 * N:2], wide[:, 1:2 * N:2], False)
+    flat = torch.randn(N, B, dtype=torch.float64, device=DEV, generator=g)
+    rows(flat.T, flat.T, False)
+    f32 = wide[:, :N].float()
+    assert b.set_load_rows(f32, f32) is False
+    assert b.set_load_rows(wide[:, :N - 1], wide[:, :N - 1]) is False
+    assert b.set_load_rows(wide[:, :N].cpu(), wide[:, :N].cpu()) is False
+    b.close()
+    m.close()
