@@ -47,8 +47,17 @@ hipError_t launch_load_rows(const double* pd, const double* qd, int64_t n, int64
                             double* qd_all, hipStream_t stream);
 
 // Scratch bytes a model needs per evaluation stream: objective partials,
-// then the half-edge records (kRec doubles per replica, branch, side).
+// then the records (kRecRoom doubles per replica and branch).
 size_t scratch_bytes(const DevModel& m);
+
+// Dynamic LDS of a branch phase that writes Jacobian and Hessian, unused: with the 5 KiB
+// of staging it leaves six waves on a compute unit (LDS is dealt in 1280-byte
+// blocks), which together write no further apart than memory takes well.
+// Waves per unit with the items in groups, 48-period set, 200-copy N-1 set and
+// 64-scenario batch: 4 29.1, 43.5, 121.3 us; 5 28.5, 43.7, 113.2; 6 28.3, 44.4,
+// 113.2; 8 29.2, 46.6, 112.5; 24 29.8, 47.2, 115.7.  The Jacobian alone is
+// slower so bounded (batch 44.8 us, 50.7).
+constexpr unsigned kBranchLds = 21 * 1280 - 10 * 64 * 8;
 
 // The batch kernel of phase 0 (branch items) or 1 (bus items) for mode 0
 // (callback set), 1 (J^T v) or 2 (flows, phase 0 only, polar only),

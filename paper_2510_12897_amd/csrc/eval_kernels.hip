@@ -187,6 +187,23 @@ __device__ __forceinline__ int32_t xcd_item(int32_t b, int32_t nb) {
     return x * q + min(x, rem) + j;
 }
 
+// The branch phase's block -> item map in sets with the Hessian, or with the
+// Jacobian and the constraints: the XCDs take turns at groups of 64
+// consecutive items.  Its waves write some thirty rows and runs of outputs
+// each, and memory takes those faster the nearer together the waves in flight
+// write (kBranchLds bounds their number): with one far range per XCD the
+// 64-scenario batch took 122.5 us (117.8 bounded), in groups of 16, 64 and 256
+// 115.6, 115.7 and 117.3 (113.6, 112.5 and 114.4).  Smaller sets keep the
+// ranges, whose neighbours share lines in one L2 (Jacobian alone 44.8 us, 46.2
+// in groups; constraints alone 43.3, 44.2), as does the bus phase.
+__device__ __forceinline__ int32_t xcd_group_item(int32_t b, int32_t nb) {
+    constexpr int32_t kGroup = 64;
+    const int32_t full = nb / (kXcd * kGroup) * (kXcd * kGroup);
+    if (b >= full) return full + xcd_item(b - full, nb - full);
+    const int32_t x = b % kXcd, j = b / kXcd;
+    return (j / kGroup * kXcd + x) * kGroup + j % kGroup;
+}
+
 // Sum over the wave in a fixed tree order; lane 0 holds the total.
 __device__ __forceinline__ double wave_sum(double v) {
     for (int s = kBlock / 2; s > 0; s >>= 1) v += __shfl_down(v, s, kBlock);
@@ -1876,7 +1893,8 @@ template <int MODE, bool RECT, bool EXT>
 __global__ void __launch_bounds__(kBlock, 6) branch_kernel(DevModel m, EvalOut o, SetGrid g) {
     __shared__ __align__(16) double stage[kRecStride * kBlock];
     int32_t kind, idx, r;
-    decode_phase1<EXT>(g, m, xcd_item(blockIdx.x, gridDim.x), kind, idx, r);
+    const int32_t b = blockIdx.x, nb = gridDim.x;
+    decode_phase1<EXT>(g, m, MODE == 0 && (o.H || (o.J && o.c)) ? xcd_group_item(b, nb) : xcd_item(b, nb), kind, idx, r);
     run_phase1<MODE, RECT, EXT>(m, o, kind, idx, r, stage);
 }
 
@@ -2023,7 +2041,8 @@ __global__ void __launch_bounds__(kBlock) batch_bus_kernel(BatchArgs a) {
 template <int MODE, bool RECT, bool EXT>
 __global__ void __launch_bounds__(kBlock) batch_branch_flat(BatchArgs a) {
     __shared__ __align__(16) double stage[kRecStride * kBlock];
-    const int32_t it = xcd_item(blockIdx.x, gridDim.x);
+    const int32_t b = blockIdx.x, nb = gridDim.x;
+    const int32_t it = MODE == 0 && (a.H || (a.J && a.C)) ? xcd_group_item(b, nb) : xcd_item(b, nb);
     if (it >= a.n_items) return;
     const BatchItem w = a.items[it];
     const BatchInst& bi = a.inst[w.inst];
@@ -2110,7 +2129,8 @@ hipError_t launch_set_form(const DevModel& m, const EvalOut& o, hipStream_t stre
         return hipGetLastError();
     }
     if (g.phase1() > 0)
-        hipLaunchKernelGGL((branch_kernel<0, RECT, EXT>), dim3(g.phase1()), dim3(kBlock), 0, stream, m, o, g);
+        hipLaunchKernelGGL((branch_kernel<0, RECT, EXT>), dim3(g.phase1()), dim3(kBlock), o.J && o.H ? kBranchLds : 0, stream,
+                           m, o, g);
     if (g.phase2() > 0)
         hipLaunchKernelGGL((bus_kernel<0, RECT, EXT>), dim3(g.phase2()), dim3(kBlock), 0, stream, m, o, g);
     return hipGetLastError();

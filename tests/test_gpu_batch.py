@@ -323,3 +323,30 @@ def test_loads_from_rows():
     assert b.set_load_rows(wide[:, :N].cpu(), wide[:, :N].cpu()) is False
     b.close()
     m.close()
+
+
+@pytest.mark.parametrize("copies", [1, 22, 23, 45])
+def test_branch_items_in_groups(copies):
+    """Branch phases of fewer items than one round of groups over the XCDs, of
+    whole rounds and of a remainder: every subset of outputs equals the whole
+    set's, and the one-launch set of the same copies."""
+    cs = synth.network(400, 700, 60, 8)  # 11 branch chunks (and one of generators) per copy
+    opf.set_single_launch_limit(0)
+    try:
+        m = opf.Model(cs, n_cont=copies - 1, outaged=synth.outages(cs, copies - 1, 2))
+    finally:
+        opf.set_single_launch_limit(4096)
+    one = opf.Model(cs, n_cont=copies - 1, outaged=synth.outages(cs, copies - 1, 2))
+    assert m.launch_shape()[0] == 2 and one.launch_shape()[0] == 1
+    g = torch.Generator(device=DEV).manual_seed(copies)
+    x = torch.rand(m.n, dtype=torch.float64, device=DEV, generator=g) + 0.5
+    y = torch.randn(m.m, dtype=torch.float64, device=DEV, generator=g)
+    names = ("f", "g", "c", "jvals", "hvals")
+    ref = dict(zip(names, one.eval_set(x, y, 0.9)))
+    for want in (names, ("jvals", "hvals"), ("c", "jvals"), ("jvals",), ("hvals",), ("c",), ("c", "hvals")):
+        out = {k: torch.full_like(ref[k], float("nan")) for k in want}
+        m.eval_set(x, y, 0.9, alloc=False, **out)
+        for k in want:
+            assert torch.equal(out[k], ref[k]), (want, k)
+    m.close()
+    one.close()
