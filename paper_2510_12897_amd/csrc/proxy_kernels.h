@@ -101,7 +101,7 @@ hipError_t prox_loss_bwd(const float* z, int B, const ProxBox& box, const ProxOb
                          const double* gX1, double obj_scale, const double* wb, int64_t n, float* dz, hipStream_t s);
 
 // The fused FP64 loss of B samples of one static polar model (one
-// workgroup each, the sample's working set in prox_loss_fused_lds bytes of
+// workgroup each, the sample's working set in at most 64 KiB of
 // LDS): loss, cvio [B]; gz [B, 2N+2G] = d loss_b / d z_b (NULL: not
 // computed); X [B, n], C [B, m] on request (NULL: not written).  loads [B, 2N]
 // holds each sample's pd then qd.
