@@ -325,7 +325,8 @@ def _make_penalty_function():
         @staticmethod
         def forward(ctx, X, pen):
             Xf = X.detach()
-            if pen.L > 0 and Xf.is_contiguous():
+            # a negated view's memory holds the values before the sign: the clone applies it
+            if pen.L > 0 and Xf.is_contiguous() and not Xf.is_neg():
                 Xf = pen.batch.flows_to(Xf, torch.empty_like(Xf))
             else:
                 Xf = pen.batch.flows(Xf.clone())

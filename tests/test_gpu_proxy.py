@@ -1230,3 +1230,22 @@ def test_fused_loss_branches_per_thread(dev, P, N, L, B):
     assert torch.allclose(v1, v0, rtol=1e-12, atol=1e-15)
     assert float((g1 - g0).abs().max()) <= 1e-6 * float(g0.abs().max())
     px.close()
+
+
+@pytest.mark.parametrize("B", [1, 3])
+def test_penalty_of_a_negated_view(dev, P, B):
+    """A contiguous view whose sign torch has not applied yet (what
+    z.conj().imag gives) has the loss, the x and the gradient of its values."""
+    pen = P.Penalty(_case(N=14, L=20, G=4, seed=3), B=B)
+    g = torch.Generator(device=dev).manual_seed(B)
+    X = torch.rand(B, pen.model.n, generator=g, device=dev, dtype=torch.float64) + 0.5
+    out = []
+    for x in (X.clone(), torch._neg_view(-X)):
+        assert x.is_contiguous()
+        x.requires_grad_(True)
+        loss = pen(x)
+        loss.sum().backward()
+        out.append((loss.detach(), pen.last["x"].clone(), x.grad.resolve_neg()))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    pen.close()
