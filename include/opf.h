@@ -595,9 +595,12 @@ int prox_train_step_bytes(const prox_mlp_desc *mlp, int B, int64_t *bytes);
  * is one prox_loss_fused takes and the MLP's output width is 2N + 2G;
  * OPF_E_ARG otherwise.  Calls on one stream run in order; concurrent calls
  * sharing a workspace race.  phase_ms: NULL, or a host array of 4 floats
- * that receives the GPU time of the forward, the loss (with its gradient
- * scaling), the backward and the Adam step, from events on the stream; the
- * call then waits for the step to finish. */
+ * that receives the GPU time of the forward, the loss (with its gradient's
+ * scaling and column sums), the backward (its products) and the update (the
+ * sums of the weight and bias gradients' parts and Adam), from events on the
+ * stream; the call then waits for the step to finish.  *step of the
+ * descriptor moves on with the update, so a call that fails before leaves it
+ * and the parameters as they were. */
 int prox_train_step(opf_model model, const prox_mlp_desc *mlp, const float *feats, const double *loads, int B,
                     double va_span, double rho, double obj_scale, float lr, float beta1, float beta2, float eps,
                     void *work, int64_t work_bytes, double *loss, double *cvio, float *phase_ms, void *stream);

@@ -83,7 +83,7 @@ struct TrainPlan {
     std::vector<bool> w_bf16, act_bf16;
     std::vector<size_t> pre, act;                 // byte offsets of each layer's pre-activation and activation
     std::vector<size_t> gw, gb;                   // its weight gradient's parts and bias gradient's column sums
-    size_t xb = 0, dz = 0, dzb = 0, d0 = 0, d1 = 0, dh = 0, total = 0;
+    size_t xb = 0, dz = 0, dzb = 0, d0 = 0, d1 = 0, dh = 0, count = 0, total = 0;
     bool x_bf16 = false, dz_bf16 = false;         // BF16 copies of the features and of d loss / d z are kept
 };
 
@@ -134,6 +134,7 @@ int make_plan(const prox_mlp_desc* mlp, int B, TrainPlan& P) {
     P.d0 = take(sizeof(float) * (size_t)B * P.maxd);
     P.d1 = take(sizeof(float) * (size_t)B * P.maxd);
     P.dh = take(sizeof(float) * (size_t)B * P.maxd);
+    P.count = take(sizeof(int32_t));
     P.total = off;
     return OPF_OK;
 }
@@ -222,13 +223,14 @@ int prox_train_step(opf_model model, const prox_mlp_desc* mlp, const float* feat
     // the loss with d loss / d z, then the mean's weight 1/B
     const float* z = reinterpret_cast<const float*>(W + P.pre[P.nl - 1]);
     float* dz = reinterpret_cast<float*>(W + P.dz);
+    int32_t* count = reinterpret_cast<int32_t*>(W + P.count);
     const opf::ProxPerm pm{model->fuse_br, model->gen_pos};
     // d loss / d z scaled by the mean's 1/B and rounded to FP32 by the loss kernel itself, then the top
-    // layer's bias sums' first pass over it (which also moves Adam's step count on)
+    // layer's bias sums' first pass over it (which also leaves this step's count for the update)
     if (!ok(opf::prox_loss_fused(model->dm, box_of(model, va_span), rows_of(model), pm, z, loads, B, rho, obj_scale,
                                  loss, cvio, nullptr, nullptr, nullptr, s, dz, 1.0 / B)) ||
         !ok(opf::prox_colsum_first(dz, B, P.D, reinterpret_cast<float*>(W + P.gb[P.nl - 1]),
-                                   P.dz_bf16 ? W + P.dzb : nullptr, mlp->step, s)))
+                                   P.dz_bf16 ? W + P.dzb : nullptr, mlp->step, count, s)))
         return hip_err(e, "prox_train_step loss");
     pe.mark(2, s);
     // backward: weight gradients (split over the batch), the bias column
@@ -260,14 +262,14 @@ int prox_train_step(opf_model model, const prox_mlp_desc* mlp, const float* feat
             if (!ok(opf::prox_gemm_mixed(1, dpre, d_bf16, fo, weight(k), P.w_bf16[k], fi, dh, fi, B, fi, fo, nullptr,
                                          nullptr, false, 0, 1, nullptr, s)) ||
                 !ok(opf::prox_gelu_bwd(pre_below, dh, reinterpret_cast<float*>(d), (int64_t)B * fi, s)) ||
-                !ok(opf::prox_colsum_first(reinterpret_cast<float*>(d), B, fi, gb, nullptr, nullptr, s)))
+                !ok(opf::prox_colsum_first(reinterpret_cast<float*>(d), B, fi, gb, nullptr, nullptr, nullptr, s)))
                 return hip_err(e, "prox_train_step dh");
             d_bf16 = false;
         }
         dpre = d;
     }
     pe.mark(3, s);
-    // the gradients' sums and Adam, kUpdateLayers layers a launch
+    // the gradients' sums and Adam, kUpdateLayers layers a launch; the last one moves Adam's step count on
     for (int k0 = 0; k0 < P.nl; k0 += opf::kUpdateLayers) {
         opf::UpdateLayers u{};
         u.n = std::min(P.nl - k0, opf::kUpdateLayers);
@@ -281,7 +283,8 @@ int prox_train_step(opf_model model, const prox_mlp_desc* mlp, const float* feat
             L.work = reinterpret_cast<const float*>(W + P.gw[k0 + q]);
             L.part = reinterpret_cast<const float*>(W + P.gb[k0 + q]);
         }
-        if (!ok(opf::prox_update(u, mlp->flat, mlp->m1, mlp->m2, mlp->flat_bf16, lr, beta1, beta2, eps, mlp->step, s)))
+        if (!ok(opf::prox_update(u, mlp->flat, mlp->m1, mlp->m2, mlp->flat_bf16, lr, beta1, beta2, eps, count,
+                                 k0 + u.n == P.nl ? mlp->step : nullptr, s)))
             return hip_err(e, "prox_train_step Adam");
     }
     if (phase_ms) {

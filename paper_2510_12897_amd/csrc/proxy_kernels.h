@@ -60,10 +60,11 @@ struct UpdateLayers {
     int32_t n, chunks;
     UpdateLayer layer[kUpdateLayers];
 };
-// Gradient sums and Adam of those layers; *step is this step's count (from 1);
-// pb (may be NULL, 8-byte aligned) receives the BF16 copy.
+// Gradient sums and Adam of those layers; *count is this step's count (from 1);
+// pb (may be NULL, 8-byte aligned) receives the BF16 copy, *step (may be NULL,
+// not count itself) the count.
 hipError_t prox_update(UpdateLayers u, float* p, float* m1, float* m2, void* pb, float lr, float b1, float b2, float eps,
-                       const int32_t* step, hipStream_t s);
+                       const int32_t* count, int32_t* step, hipStream_t s);
 // out [M, N] (BF16) = (A B) * gelu'(pre) for row-major A [M, K], B [K, N]
 // (either BF16), pre [M, N]; part [ceil(M / 128), N] = the column sums of
 // each 128-row block of the FP32 product (prox_colsum's first pass).
@@ -75,8 +76,10 @@ hipError_t prox_colsum_parts(const float* part, int chunks, int N, float* out, f
 hipError_t prox_gelu_bwd(const float* pre, const float* dact, float* dpre, int64_t n, hipStream_t s);
 hipError_t prox_colsum(const float* X, int M, int N, float* part, float* out, float scale, hipStream_t s);
 // prox_colsum's first pass only: part [ceil(M / 128), N]; Xb (may be NULL)
-// receives X rounded to BF16; *count (may be NULL) is moved on by one
-hipError_t prox_colsum_first(const float* X, int M, int N, float* part, void* Xb, int32_t* count, hipStream_t s);
+// receives X rounded to BF16; *next (may be NULL, then step too) receives
+// *step + 1
+hipError_t prox_colsum_first(const float* X, int M, int N, float* part, void* Xb, const int32_t* step, int32_t* next,
+                             hipStream_t s);
 hipError_t prox_adam(float* p, const float* g, float* m1, float* m2, int64_t n, float lr, float b1, float b2, float eps,
                      int step, void* pb, hipStream_t s);
 hipError_t prox_adam_dev(float* p, const float* g, float* m1, float* m2, int64_t n, float lr, float b1, float b2,

@@ -688,12 +688,13 @@ __global__ void gelu_bwd_kernel(const float* __restrict__ pre, const float* __re
 // each sum in row order, then the four groups in order.  Pass 2: the chunk
 // sums of each column the same way (chunks g, g + 4, ..., then the groups).
 constexpr int COLSUM_ROWS = 128;
-// Xb (may be NULL): X rounded to BF16, on the way.  count (may be NULL): a
-// counter this launch moves on by one, for a later one to read.
+// Xb (may be NULL): X rounded to BF16, on the way.  next (may be NULL):
+// receives *step + 1, for a later launch to read.
 __global__ void __launch_bounds__(256) colsum_partial_kernel(const float* __restrict__ X, int M, int N,
                                                              float* __restrict__ part, __bf16* __restrict__ Xb,
-                                                             int32_t* __restrict__ count) {
-    if (count && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *count += 1;
+                                                             const int32_t* __restrict__ step,
+                                                             int32_t* __restrict__ next) {
+    if (next && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *next = *step + 1;
     __shared__ float s[4][64];
     const int c = threadIdx.x % 64, g = threadIdx.x / 64;
     const int j = blockIdx.x * 64 + c;
@@ -835,9 +836,10 @@ __global__ void __launch_bounds__(256) adam_dev4_kernel(float* __restrict__ p, c
 // update those.  Bound by memory: per weight 4 bytes of each part, 24 of
 // parameter and moments, 2 of the BF16 copy.  The gradient itself never
 // reaches memory, and one launch replaces a sum per layer, Adam and the step
-// count's own (4,096-sample step: 348 -> 334 us; this kernel 31 us for 145 MB).  The step count is the
-// one that this step's column-sum pass already moved on.  VEC: 16-byte
-// accesses of parameters and moments.
+// count's own (4,096-sample step: 348 -> 334 us; this kernel 31 us for 145 MB).  This step's count is the
+// one that its column-sum pass left in the scratch; the launch that has step
+// stores it there, so a step that fails before its update leaves Adam's count
+// as it was.  VEC: 16-byte accesses of parameters and moments.
 template <bool VEC>
 __device__ __forceinline__ float4 load4(const float* p) {
     if constexpr (VEC)
@@ -859,14 +861,17 @@ __device__ __forceinline__ void store4(float* p, const float4& v) {
 template <bool VEC>
 __global__ void __launch_bounds__(256) update_kernel(UpdateLayers u, float* __restrict__ p, float* __restrict__ m1,
                                                      float* __restrict__ m2, __bf16* __restrict__ pb, float lr,
-                                                     float b1, float b2, float eps, const int32_t* __restrict__ step) {
+                                                     float b1, float b2, float eps,
+                                                     const int32_t* __restrict__ count, int32_t* __restrict__ step) {
     __shared__ float corr[2], sg[4][64];
     const int blk = blockIdx.x;
     int k = 0;
     while (k + 1 < u.n && blk >= u.layer[k + 1].first) k++;
     const UpdateLayer& L = u.layer[k];
     if (threadIdx.x == 0) {
-        const float t = (float)*step;
+        const int32_t n = *count;
+        if (step && blk == 0) *step = n;
+        const float t = (float)n;
         corr[0] = 1.f - powf(b1, t);
         corr[1] = 1.f - powf(b2, t);
     }
@@ -1813,7 +1818,7 @@ hipError_t prox_gemm_split_parts(int variant, const void* A, bool a_bf16, int ld
 }
 
 hipError_t prox_update(UpdateLayers u, float* p, float* m1, float* m2, void* pb, float lr, float b1, float b2, float eps,
-                       const int32_t* step, hipStream_t s) {
+                       const int32_t* count, int32_t* step, hipStream_t s) {
     int blocks = 0;
     for (int k = 0; k < u.n; k++) {
         UpdateLayer& L = u.layer[k];
@@ -1823,7 +1828,7 @@ hipError_t prox_update(UpdateLayers u, float* p, float* m1, float* m2, void* pb,
     }
     const bool vec = aligned16(p) && aligned16(m1) && aligned16(m2);
     hipLaunchKernelGGL(vec ? update_kernel<true> : update_kernel<false>, dim3(blocks), dim3(256), 0, s, u, p, m1, m2,
-                       static_cast<__bf16*>(pb), lr, b1, b2, eps, step);
+                       static_cast<__bf16*>(pb), lr, b1, b2, eps, count, step);
     return hipGetLastError();
 }
 
@@ -1839,17 +1844,19 @@ hipError_t prox_gelu_bwd(const float* pre, const float* dact, float* dpre, int64
     return hipGetLastError();
 }
 
-hipError_t prox_colsum_first(const float* X, int M, int N, float* part, void* Xb, int32_t* count, hipStream_t s) {
+hipError_t prox_colsum_first(const float* X, int M, int N, float* part, void* Xb, const int32_t* step, int32_t* next,
+                             hipStream_t s) {
     const int chunks = (M + COLSUM_ROWS - 1) / COLSUM_ROWS;
     hipLaunchKernelGGL(colsum_partial_kernel, dim3((N + 63) / 64, chunks), dim3(256), 0, s, X, M, N, part,
-                       static_cast<__bf16*>(Xb), count);
+                       static_cast<__bf16*>(Xb), step, next);
     return hipGetLastError();
 }
 
 hipError_t prox_colsum(const float* X, int M, int N, float* part, float* out, float scale, hipStream_t s) {
     const int chunks = (M + COLSUM_ROWS - 1) / COLSUM_ROWS;
     hipLaunchKernelGGL(colsum_partial_kernel, dim3((N + 63) / 64, chunks), dim3(256), 0, s, X, M, N, part,
-                       static_cast<__bf16*>(nullptr), static_cast<int32_t*>(nullptr));
+                       static_cast<__bf16*>(nullptr), static_cast<const int32_t*>(nullptr),
+                       static_cast<int32_t*>(nullptr));
     hipLaunchKernelGGL(colsum_final_kernel, dim3((N + 63) / 64), dim3(256), 0, s, part, chunks, N, out, scale);
     return hipGetLastError();
 }
