@@ -370,8 +370,8 @@ int opf_batch_set_load_rows(opf_batch batch, const double *pd, const double *qd,
 int opf_batch_flows(opf_batch batch, double *X, void *stream);
 
 /* OUT = X with the arc variables so overwritten, in one launch; OUT is X
- * itself or apart from it.  Static polar models with branches only
- * (OPF_E_ARG otherwise). */
+ * itself or apart from it (OPF_E_ARG where they overlap otherwise).  Static
+ * polar models with branches only (OPF_E_ARG otherwise). */
 int opf_batch_flows_to(opf_batch batch, const double *X, double *OUT, void *stream);
 
 /* ------------------------------------------------ learned warm-start proxy */

@@ -365,6 +365,11 @@ int opf_batch_flows_to(opf_batch b, const double* X, double* OUT, void* stream) 
     if (!valid(b)) return set_err(OPF_E_STATE, "invalid or destroyed batch handle");
     if (!X || !OUT) return set_err(OPF_E_ARG, "X and OUT must be non-NULL");
     if (b->rect || !b->flat) return set_err(OPF_E_ARG, "opf_batch_flows_to takes static polar models only");
+    // one instance's copy would race with another's reads
+    const uintptr_t xa = reinterpret_cast<uintptr_t>(X), oa = reinterpret_cast<uintptr_t>(OUT);
+    const size_t bytes = sizeof(double) * (size_t)b->xoff.back();
+    if (xa != oa && xa < oa + bytes && oa < xa + bytes)
+        return set_err(OPF_E_ARG, "OUT must be X itself or apart from it");
     DeviceGuard dg(b->device);
     if (dg.err != hipSuccess) return hip_err(dg.err, "hipSetDevice");
     opf::BatchArgs a{};

@@ -350,3 +350,24 @@ def test_branch_items_in_groups(copies):
             assert torch.equal(out[k], ref[k]), (want, k)
     m.close()
     one.close()
+
+
+@pytest.mark.parametrize("N,L,G", [(3, 3, 1), (30, 29, 7)])
+def test_flows_into_an_overlapping_array_are_refused(N, L, G):
+    """OUT may be X or lie apart from it (end to end included); any other
+    overlap would race between the instances and is an error."""
+    m = opf.Model(synth.network(N, L, G, 6))
+    b = opf.Batch([m], np.zeros(3, np.int32))
+    buf = torch.rand(2 * b.n, dtype=torch.float64, device=DEV) + 0.5
+    keep = buf.clone()
+    for off in (1, m.n, b.n - 1):
+        for lo, hi in ((0, off), (off, 0)):
+            with pytest.raises(opf.OPFError, match="apart") as ei:
+                b.flows_to(buf[lo:lo + b.n], buf[hi:hi + b.n])
+            assert ei.value.code == opf.OPF_E_ARG
+    assert torch.equal(buf, keep)
+    want = b.flows(keep[:b.n].clone())
+    assert torch.equal(b.flows_to(buf[:b.n], buf[b.n:]), want)
+    assert torch.equal(b.flows_to(buf[:b.n], buf[:b.n]), want)
+    b.close()
+    m.close()
