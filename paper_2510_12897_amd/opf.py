@@ -348,7 +348,10 @@ def _stream():
     """The current stream of torch's current device, as an integer handle."""
     torch = _torch_module or _torch()
     if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:  # private names, which another torch build may not have
+            pass
     return torch.cuda.current_stream().cuda_stream  # initialises the device or raises
 
 
