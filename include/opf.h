@@ -491,7 +491,8 @@ int prox_squash_bwd(opf_model model, const float *z, int B, double va_span, cons
  * vjp != 0 the weights of prox_vjp_weights (computed in the same pass), so
  * that J^T W is the whole constraint part of the gradient.  With vjp != 0
  * and 4L <= 7680, gpq may be NULL: d pen / d (p, q), needed only by those
- * weights, then stays on chip (OPF_E_ARG for a NULL gpq otherwise). */
+ * weights, then stays on chip (OPF_E_ARG for a NULL gpq otherwise).  An
+ * instance's outputs are the same bits in every batch. */
 int prox_penalty(opf_model model, const double *C, const double *X, const double *F, double obj_scale, double rho,
                  int B, int vjp, double *pen, double *cvio, double *W, double *gpq, void *stream);
 
@@ -536,7 +537,7 @@ int prox_loss_bwd(opf_model model, const float *z, int B, double va_span, const 
  * receive x (with the arc flows) and c(x) when non-NULL.  The arc values,
  * the thermal and angle rows and X equal those launches' bits; the balance
  * rows, loss and gz are summed in another fixed order (rounding-level
- * differences; the same bits on every run).  Takes a static polar model
+ * differences; the same bits on every run and in every batch).  Takes a static polar model
  * without storage units or devices (prox_loss_fused_fits); OPF_E_ARG
  * otherwise.  Buffers are device memory the caller owns. */
 int prox_loss_fused(opf_model model, const float *z, int B, double va_span, const double *loads, double rho,

@@ -1249,3 +1249,59 @@ def test_penalty_of_a_negated_view(dev, P, B):
     for a, b in zip(*out):
         assert torch.equal(a, b)
     pen.close()
+
+
+# both launch shapes of each network size (threads per sample by the batch), whole and partial last rounds
+@pytest.mark.parametrize("N,L,B", [(14, 20, 1030), (64, 64, 1025), (60, 257, 515), (300, 406, 600), (90, 512, 513),
+                                   (90, 520, 1100)])
+def test_fused_loss_of_a_sample_does_not_depend_on_its_batch(dev, P, N, L, B):
+    """The loss, Cvio, x, c and gradient of the first samples scored alone, in
+    batches on both sides of the launch's lines and all together: the same bits."""
+    px = P.WarmStartProxy(synth.network(N, L, 6, 11), B=B, width=16, depth=1, seed=2)
+    gen = torch.Generator(device=dev).manual_seed(N + L)
+    loads, _ = px.sample(gen)
+    z = torch.randn(B, 2 * px.N + 2 * px.G, generator=gen, device=dev) * 1.5
+
+    def score(b):
+        px.pen.B = b
+        zb = z[:b].clone().requires_grad_(True)
+        lb = P._fun("loss").apply(zb, px, loads[:b], True)
+        lb.sum().backward()
+        return lb.detach().clone(), px.pen.last["cvio"].clone(), px.pen.last["x"].clone(), px.pen.last["c"].clone(), zb.grad
+
+    assert px.pen.fused
+    whole = score(B)
+    for b in (1, 5, 512, 513, 1024):
+        if b < B:
+            for got, want in zip(score(b), whole):
+                assert torch.equal(got, want[:b]), b
+    px.pen.B = B
+    px.close()
+
+
+@pytest.mark.parametrize("N,L", [(14, 20), (100, 130), (300, 410), (370, 481)])
+def test_penalty_of_an_instance_does_not_depend_on_its_batch(dev, P, N, L):
+    """prox_penalty's outputs for the first instances of 515 alone, in batches on
+    both sides of the launch's line and all together: the same bits."""
+    from paper_2510_12897_amd import opf as binding
+    md = binding.Model(synth.network(N, L, max(2, N // 5), 7))
+    g = torch.Generator(device=dev).manual_seed(N)
+    top = 515
+    C = torch.randn(top, md.m, dtype=torch.float64, device=dev, generator=g)
+    X = torch.randn(top, md.n, dtype=torch.float64, device=dev, generator=g)
+    F = torch.randn(top, dtype=torch.float64, device=dev, generator=g)
+
+    def score(b, vjp):
+        out = [torch.full((b, k), float("nan"), dtype=torch.float64, device=dev) for k in (1, 1, md.m, 4 * L)]
+        binding._check(binding.lib().prox_penalty(md.handle, C.data_ptr(), X.data_ptr(), F.data_ptr(), 1e-3, 10.0, b,
+                                                  vjp, *[t.data_ptr() for t in out],
+                                                  torch.cuda.current_stream().cuda_stream))
+        return out
+
+    for vjp in (0, 1):
+        whole = score(top, vjp)
+        assert not any(bool(t.isnan().any()) for t in whole)
+        for b in (1, 7, 512, 513):
+            for got, want in zip(score(b, vjp), whole):
+                assert torch.equal(got, want[:b]), (b, vjp)
+    md.close()
