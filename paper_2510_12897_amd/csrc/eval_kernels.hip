@@ -870,8 +870,13 @@ __device__ void wave_task(const DevModel& m, const EvalOut& o, int32_t w, int32_
         // into a register another type's load is still filling would make
         // the wave wait for that load.
         double gs, bs, vm_i, vr_i, pd, qd, yp, yq, ymag, gp, gq;
-        double2 ra, rb;
+        double2 ra, rb, rc;
         HeIn e;
+        // the half-edge's arc values: in registers of their own, or in the
+        // storage lanes'; either way 80 registers at most, six waves per SIMD
+        // (with 81 the 64-scenario batch's constraints took 43.8 us, 40.9 so;
+        // the other way round 79 and 77 are both 81)
+        double &ep = EXT ? gp : rc.x, &eq = EXT ? gq : rc.y;
         RHeIn re;
         int32_t jrow, hva0, hvm0, nlo, nd;  // the head's per-bus offsets (compact slots)
         if (type == SK_HEAD) {
@@ -913,14 +918,14 @@ __device__ void wave_task(const DevModel& m, const EvalOut& o, int32_t w, int32_
                 ra = ld(rec, q + (side ? 3 : 1));
                 rb = ld(rec, q + 2);
                 if (wantC) {
-                    const double2 rc = ld(rec, q + 4 * side);
-                    gp = rc.x;
-                    gq = rc.y;
+                    rc = ld(rec, q + 4 * side);
+                    ep = rc.x;
+                    eq = rc.y;
                 }
             } else if (wantC) {
                 const uint32_t a = ref + (side ? (uint32_t)m.L : 0u);
-                gp = ld(o.x + m.x_p + 2 * (int64_t)m.L * r, a);
-                gq = ld(o.x + m.x_q + 2 * (int64_t)m.L * r, a);
+                ep = ld(o.x + m.x_p + 2 * (int64_t)m.L * r, a);
+                eq = ld(o.x + m.x_q + 2 * (int64_t)m.L * r, a);
             }
         } else if (EXT && type == SK_GEN && (kind & 4)) {
             // a storage unit: ps, qs (and for its (vm, vm) term the loss
@@ -976,8 +981,8 @@ __device__ void wave_task(const DevModel& m, const EvalOut& o, int32_t w, int32_
                 v[R_UW] = rb.y;
             }
             if (wantC) {
-                v[R_P] = gp;
-                v[R_Q] = gq;
+                v[R_P] = ep;
+                v[R_Q] = eq;
             }
         } else if (EXT && type == SK_GEN && (kind & 4)) {  // storage: +ps, +qs
             if (wantC) {
