@@ -1641,6 +1641,38 @@ void launch_gemm(int variant, dim3 grid, hipStream_t s, const TA* A, int lda, co
     }
 }
 
+constexpr int kUnits = 256;
+int64_t tile_count(int M, int N, int z, int bm, int bn) {
+    return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * z;
+}
+// Whether 128 x 128 tiles, two workgroups per compute unit, come in whole
+// rounds: the last one more than half full.
+bool whole_rounds(int64_t wide) {
+    return wide >= 2 * kUnits && (wide % (2 * kUnits) == 0 || wide % (2 * kUnits) > kUnits);
+}
+// Whether an FP32 A takes the tiled kernels (out: bytes stored per row and
+// column beside C's 4, for the activation).  Its tiles (128 x 128 beyond a
+// round) fit one workgroup per unit, and every wave column reads and rounds
+// A's values again, so beyond one round they lose to the register-staged
+// kernel (which rounds them once, two or three workgroups per unit) where
+// its rounds are whole: forward 8192 x 1024 x 1024 30.6 us, 35.4 in tiles,
+// 4096 x 4096 x 4096 180 and 196; up to 384 tiles (its 64-column tiles are one
+// round) only for short k loops: 6000 x 1024 x 256 13.7 and 15.5, x 1024 30.5
+// and 29.7; and where one k tile is all (4096 x 512 x 64 5.7 and 6.0).  Between
+// its rounds the tiles win (12000 x 1024 x 1024 with GELU 61.9 and 56.8;
+// 10000 x 600 x 1024 48.0 and 35.6), with an activation once A and the
+// outputs pass the last-level cache (32768 x 1024 x 600 145 and 112, x 256
+// 68 and 74), and in the dh product (B read by the transpose read) from 1024
+// k values on (8192 x 2048 x 2048 112.8, 107.7).
+bool tiled_fp32(int variant, int M, int N, int k, int splits, int out) {
+    const int64_t wide = tile_count(M, N, splits, 128, 128);
+    if (!out && k <= 64 && tile_count(M, N, splits, 64, 64) > kUnits) return false;
+    if (wide <= kUnits) return true;
+    if (whole_rounds(wide))
+        return (variant == 1 && k >= 1024) || (out && (int64_t)M * (4 * (int64_t)k + (4 + out) * (int64_t)N) > (256 << 20));
+    return wide > 3 * kUnits / 2 || k >= 1024;
+}
+
 // Whether a product's operands allow the tiled kernels: 16-byte copies of
 // whole chunks at 16-byte addresses (a row-contiguous operand: rows and
 // leading dimension multiples of 8; a k-contiguous one: k values likewise, 4
@@ -1652,27 +1684,32 @@ bool tiled_operand(const void* p, bool bf16, bool k_cont, int ld, int rows, int 
     const int unit = bf16 ? 8 : 4;
     return ld % unit == 0 && (k_cont ? K % unit == 0 : bf16 && rows % 8 == 0);
 }
-bool tiled_product(int variant, const void* A, bool a_bf16, int lda, const void* B, bool b_bf16, int ldb, int M, int N,
-                   int K) {
+bool tiled_operands(int variant, const void* A, bool a_bf16, int lda, const void* B, bool b_bf16, int ldb, int M, int N,
+                    int K) {
     if (variant > 2 || !b_bf16 || (variant == 2 && !a_bf16)) return false;
     return tiled_operand(A, a_bf16, variant != 2, lda, M, K) && tiled_operand(B, b_bf16, variant == 0, ldb, N, K);
+}
+bool tiled_product(int variant, const void* A, bool a_bf16, int lda, const void* B, bool b_bf16, int ldb, int M, int N,
+                   int K, int splits, int out) {
+    return tiled_operands(variant, A, a_bf16, lda, B, b_bf16, ldb, M, N, K) &&
+           (a_bf16 || tiled_fp32(variant, M, N, K / splits, splits, out));
 }
 
 // Tile shapes: the smallest that needs no more workgroups than the chip has
 // compute units (256), else the widest.  A workgroup's time is its k loop,
 // bound by the rate a compute unit fills its LDS (about 45 bytes a clock from
 // L2, less from beyond), and a smaller tile spreads the operands over more of
-// them; beyond one round the wide tile moves the fewest bytes per product.
+// them; beyond one round a wide tile moves the fewest bytes per product.
 // Forward with GELU, 1024 k: 64 rows x 1024 columns 14.7 us in the
 // register-staged kernel, 6.2 (32 x 32 tiles), 6.7 (64 x 64); 1024 rows 8.7
 // (64 x 64), 9.4 (32 x 32), 10.2 (128 x 64), before 19.9; 4096 rows 16.6
-// (128 x 64, two workgroups per unit: one's epilogue beside the other's
-// products), 17.3 (128 x 128), 21.2 (64 x 64), before 25.0.
-constexpr int kUnits = 256;
-int64_t tile_count(int M, int N, int z, int bm, int bn) {
-    return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * z;
-}
-
+// (128 x 64, two workgroups per unit), 17.3 (128 x 128, one), 21.2 (64 x 64),
+// before 25.0.  Where 128 x 128 tiles of two stages, four waves of 64 x 64 and
+// two workgroups per unit come in whole rounds they read a quarter fewer bytes
+// per product: 4096 x 4096 x 4096 195 -> 136 us (the register-staged kernel
+// 164; 128 x 128 of three stages and eight waves 170), 8192 x 1024 x 1024 27.2 ->
+// 23.7 (28.3).  Where the last half of the columns would be empty, in between, and under a GELU epilogue of a short k loop, the
+// narrower tile's smaller steps win (16384 x 600 x 600 with GELU 32.3, 39.3).
 template <typename TA, bool AK, bool BK, int TM, int TN, int WM, int WN, int ST>
 void tile_launch(hipStream_t s, const TA* A, int lda, const __bf16* B, int ldb, float* C, int ldc, int M, int N, int K,
                  int kchunk, const float* bias, void* act, bool act_bf16, int accumulate, int splits, float* work) {
@@ -1689,8 +1726,13 @@ void tile_shape(hipStream_t s, const TA* A, int lda, const __bf16* B, int ldb, f
     else if (tile_count(M, N, splits, 64, 64) <= kUnits)
         tile_launch<TA, AK, BK, 64, 64, 2, 2, 4>(s, A, lda, B, ldb, C, ldc, M, N, K, kchunk, bias, act, act_bf16,
                                                  accumulate, splits, work);
-    else if constexpr (sizeof(TA) == 4)  // twice the bytes per stage: one workgroup of 144 KiB per unit
-        tile_launch<TA, AK, BK, 128, 128, 2, 4, 3>(s, A, lda, B, ldb, C, ldc, M, N, K, kchunk, bias, act, act_bf16,
+    else if constexpr (sizeof(TA) == 4)  // twice the bytes per stage: one workgroup of 144 KiB per unit; each
+                                         // value of A read and rounded by two waves (by four: 5 to 12 % slower)
+        tile_launch<TA, AK, BK, 128, 128, 4, 2, 3>(s, A, lda, B, ldb, C, ldc, M, N, K, kchunk, bias, act, act_bf16,
+                                                   accumulate, splits, work);
+    else if (const int64_t wide = tile_count(M, N, splits, 128, 128);
+             whole_rounds(wide) && (!act || K >= 1024) && 15 * wide <= 8 * tile_count(M, N, splits, 128, 64))
+        tile_launch<TA, AK, BK, 128, 128, 2, 2, 2>(s, A, lda, B, ldb, C, ldc, M, N, K, kchunk, bias, act, act_bf16,
                                                    accumulate, splits, work);
     else
         tile_launch<TA, AK, BK, 128, 64, 4, 2, 3>(s, A, lda, B, ldb, C, ldc, M, N, K, kchunk, bias, act, act_bf16,
@@ -1801,7 +1843,7 @@ hipError_t prox_gemm_gelu_bwd(const void* A, bool a_bf16, int lda, const void* B
     // Column width by the tile_shape rule (the column sums fix 128 rows):
     // 4096 x 1024 x 1024 19.6 us with 64 columns, 21.0 with 128, before 29.4;
     // 1024 rows 10.7 with 32, 11.7 with 64, before 24.9.
-    if (tiled_product(1, A, a_bf16, lda, B, b_bf16, ldb, M, N, K)) {
+    if (tiled_operands(1, A, a_bf16, lda, B, b_bf16, ldb, M, N, K)) {
         const __bf16* b = static_cast<const __bf16*>(B);
         auto go = [&](auto kernel, const auto* a, int cols, int threads) {
             hipLaunchKernelGGL(kernel, dim3((N + cols - 1) / cols, (M + BM - 1) / BM, 1), dim3(threads), 0, s, a, lda, b,
@@ -1835,7 +1877,7 @@ hipError_t prox_colsum_parts(const float* part, int chunks, int N, float* out, f
 hipError_t prox_gemm_mixed(int variant, const void* A, bool a_bf16, int lda, const void* B, bool b_bf16, int ldb,
                            float* C, int ldc, int M, int N, int K, const float* bias, void* act, bool act_bf16,
                            int accumulate, int splits, float* work, hipStream_t s) {
-    if (tiled_product(variant, A, a_bf16, lda, B, b_bf16, ldb, M, N, K)) {
+    if (tiled_product(variant, A, a_bf16, lda, B, b_bf16, ldb, M, N, K, splits, act ? (act_bf16 ? 2 : 4) : 0)) {
         tile_product(variant, A, a_bf16, lda, B, ldb, C, ldc, M, N, K, split_chunk(K, splits), bias, act, act_bf16,
                      accumulate, splits, splits > 1 ? work : nullptr, s);
         if (splits > 1)
@@ -1852,7 +1894,7 @@ hipError_t prox_gemm_mixed(int variant, const void* A, bool a_bf16, int lda, con
 
 hipError_t prox_gemm_split_parts(int variant, const void* A, bool a_bf16, int lda, const void* B, bool b_bf16, int ldb,
                                  int M, int N, int K, int splits, float* work, hipStream_t s) {
-    if (tiled_product(variant, A, a_bf16, lda, B, b_bf16, ldb, M, N, K)) {
+    if (tiled_product(variant, A, a_bf16, lda, B, b_bf16, ldb, M, N, K, splits, 0)) {
         tile_product(variant, A, a_bf16, lda, B, ldb, nullptr, N, M, N, K, split_chunk(K, splits), nullptr, nullptr,
                      false, 0, splits, work, s);
         return hipGetLastError();

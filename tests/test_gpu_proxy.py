@@ -1305,3 +1305,13 @@ def test_penalty_of_an_instance_does_not_depend_on_its_batch(dev, P, N, L):
             for got, want in zip(score(b, vjp), whole):
                 assert torch.equal(got, want[:b]), (b, vjp)
     md.close()
+
+
+# beyond one round of wide tiles: 800 (whole rounds of two workgroups per unit: the two-stage 128 x 128 tile, under an
+# activation from 1,024 k values on), 272 and 400 (FP32 A leaves or keeps the tiles), each with remainders
+@pytest.mark.parametrize("shape", [(3176, 4072, 72), (3176, 4072, 1032), (2056, 2112, 136), (3176, 2008, 200)])
+@pytest.mark.parametrize("variant", [0, 1, 2])
+def test_tiled_products_beyond_one_round(dev, P, variant, shape):
+    """The products of test_tiled_products_at_tile_edges at sizes of several
+    rounds: the same bits as the register-staged kernel."""
+    test_tiled_products_at_tile_edges(dev, P, variant, shape, 1)
