@@ -539,7 +539,7 @@ tile_gelu_bwd_kernel(const TA* __restrict__ A, int lda, const TB* __restrict__ B
     f32x16 acc[T::NA][T::NB];
     T::run(A, lda, B, ldb, M, N, i0, j0, 0, K, smem, acc);
     // this thread's pre-activations (columns clamped to valid places, used inside N), in flight while the tile is
-    // staged; rows past M are left out (4 x 512 x 64 5.6 -> 4.7 us) of a part tile only: the branches cost a whole
+    // staged; rows past M are left out (4 x 512 x 64 5.5 -> 3.8 us) of a part tile only: the branches cost a whole
     // one 0.4 us
     constexpr int NR = BM * C4 / NT;
     const int c4 = threadIdx.x % C4, lr0 = threadIdx.x / C4, jc = j0 + c4 * 4, rows = min(BM, M - i0);
@@ -1142,7 +1142,7 @@ __device__ __forceinline__ double wave_sums(const double (&v)[N], double& mx) {
 // Bound by the latency of its loads: a thread's loop holds kPenRows rows'
 // loads in flight, and few instances of many rows take more threads each (256
 // instances of 1,000 buses, 70 MB: 57.2 us with 256 threads and one row at a
-// time, 33.5 us with four rows, 19.0 us with 1,024 threads as well).
+// time, 33.5 us with four rows, 18.6 us with 1,024 threads as well).
 constexpr int kPenRows = 4;
 template <int NT, int LANES>
 __global__ void __launch_bounds__(NT) penalty_kernel(const double* __restrict__ C, const double* __restrict__ X,
@@ -2021,12 +2021,15 @@ hipError_t prox_penalty(const double* C, const double* X, const double* F, doubl
                         double rho, int B, double* pen, double* cvio, double* W, double* gpq, int vjp, hipStream_t s) {
     const size_t lds = gpq ? 0 : sizeof(double) * (size_t)rows.npq;
     // 1,024 threads per instance where each has a row of its own and two
-    // instances per compute unit (32 waves) hold the whole batch.  100 buses
-    // (1,153 rows): 256 instances 5.6 us with 256 threads, 5.1 us with 1,024;
-    // 1,024 instances 9.5 and 11.3 us.  14 buses (162 rows), 256 instances: 3.7
-    // and 4.4 us.  1,000 buses: 256 instances 33.5 and 19.0 us, 1,024 even.
+    // instances per compute unit (32 waves) hold the whole batch, else 512
+    // where each has four.  100 buses (1,111 rows): 256 instances 5.6 us with
+    // 256 threads, 5.1 us with 1,024; 1,024 instances 9.5 and 11.0 us; 4,096
+    // 25.6, 30.1 with 512, 34.3 with 1,024.  14 buses (169 rows), 256
+    // instances: 3.6 and 4.4 us.  300 buses (3,471 rows): 1,024 instances 22.2,
+    // 21.2, 21.2 us with 256, 512 and 1,024; 4,096 114, 108, 111.  1,000 buses:
+    // 256 instances 33.5 and 18.6 us with 256 and 1,024.
     // The lanes of the sum follow the rows alone (four a thread cost 0.3 us at
-    // 100 buses and 513 instances, nothing at 1,000).
+    // 100 buses and 513 instances).
     auto go = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3(B), dim3(threads), lds, s, C, X, F, obj_scale, rows, rho, pen, cvio, W, gpq, vjp);
     };
@@ -2034,6 +2037,8 @@ hipError_t prox_penalty(const double* C, const double* X, const double* F, doubl
         go(penalty_kernel<256, 256>, 256);
     else if (B <= 2 * kUnits)
         go(penalty_kernel<1024, 1024>, 1024);
+    else if (rows.m >= 2048)
+        go(penalty_kernel<512, 1024>, 512);
     else
         go(penalty_kernel<256, 1024>, 256);
     return hipGetLastError();
