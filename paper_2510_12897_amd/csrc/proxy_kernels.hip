@@ -2021,13 +2021,15 @@ hipError_t prox_penalty(const double* C, const double* X, const double* F, doubl
                         double rho, int B, double* pen, double* cvio, double* W, double* gpq, int vjp, hipStream_t s) {
     const size_t lds = gpq ? 0 : sizeof(double) * (size_t)rows.npq;
     // 1,024 threads per instance where each has a row of its own and two
-    // instances per compute unit (32 waves) hold the whole batch, else 512
-    // where each has four.  100 buses (1,111 rows): 256 instances 5.6 us with
+    // instances per compute unit (32 waves) hold the whole batch, or where each
+    // has four rows; else 512 where each of those has four.  100 buses (1,111 rows): 256 instances 5.6 us with
     // 256 threads, 5.1 us with 1,024; 1,024 instances 9.5 and 11.0 us; 4,096
     // 25.6, 30.1 with 512, 34.3 with 1,024.  14 buses (169 rows), 256
     // instances: 3.6 and 4.4 us.  300 buses (3,471 rows): 1,024 instances 22.2,
-    // 21.2, 21.2 us with 256, 512 and 1,024; 4,096 114, 108, 111.  1,000 buses:
-    // 256 instances 33.5 and 18.6 us with 256 and 1,024.
+    // 21.2, 21.2 us with 256, 512 and 1,024; 4,096 114, 108, 111.  500 buses
+    // (5,551 rows), 4,096 instances: 188, 176, 170.  1,000 buses: 256 instances
+    // 33.5 and 18.6 us with 256 and 1,024, 1,024 instances 86.5 (90.2 with 512)
+    // and 86.8.
     // The lanes of the sum follow the rows alone (four a thread cost 0.3 us at
     // 100 buses and 513 instances).
     auto go = [&](auto kernel, int threads) {
@@ -2035,7 +2037,7 @@ hipError_t prox_penalty(const double* C, const double* X, const double* F, doubl
     };
     if (rows.m < 1024)
         go(penalty_kernel<256, 256>, 256);
-    else if (B <= 2 * kUnits)
+    else if (B <= 2 * kUnits || rows.m >= 4096)
         go(penalty_kernel<1024, 1024>, 1024);
     else if (rows.m >= 2048)
         go(penalty_kernel<512, 1024>, 512);

@@ -1279,7 +1279,7 @@ def test_fused_loss_of_a_sample_does_not_depend_on_its_batch(dev, P, N, L, B):
     px.close()
 
 
-@pytest.mark.parametrize("N,L", [(14, 20), (100, 130), (300, 410), (370, 481)])
+@pytest.mark.parametrize("N,L", [(14, 20), (100, 130), (190, 250), (300, 410), (370, 481)])
 def test_penalty_of_an_instance_does_not_depend_on_its_batch(dev, P, N, L):
     """prox_penalty's outputs for the first instances of 515 alone, in batches on
     both sides of the launch's line and all together: the same bits."""
