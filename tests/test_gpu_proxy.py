@@ -1308,10 +1308,110 @@ def test_penalty_of_an_instance_does_not_depend_on_its_batch(dev, P, N, L):
 
 
 # beyond one round of wide tiles: 800 (whole rounds of two workgroups per unit: the two-stage 128 x 128 tile, under an
-# activation from 1,024 k values on), 272 and 400 (FP32 A leaves or keeps the tiles), each with remainders
-@pytest.mark.parametrize("shape", [(3176, 4072, 72), (3176, 4072, 1032), (2056, 2112, 136), (3176, 2008, 200)])
+# activation from 1,024 k values on), 272 and 400 (FP32 A leaves or keeps the tiles), 936 with the parts of a split
+# counted, each with remainders
+@pytest.mark.parametrize("shape,splits", [((3176, 4072, 72), 1), ((3176, 4072, 1032), 1), ((2056, 2112, 136), 1),
+                                          ((3176, 2008, 200), 1), ((1032, 1000, 4104), 13)])
 @pytest.mark.parametrize("variant", [0, 1, 2])
-def test_tiled_products_beyond_one_round(dev, P, variant, shape):
+def test_tiled_products_beyond_one_round(dev, P, variant, shape, splits):
     """The products of test_tiled_products_at_tile_edges at sizes of several
     rounds: the same bits as the register-staged kernel."""
-    test_tiled_products_at_tile_edges(dev, P, variant, shape, 1)
+    test_tiled_products_at_tile_edges(dev, P, variant, shape, splits)
+
+
+@pytest.mark.parametrize("variant", [0, 1, 2])
+@pytest.mark.parametrize("shape", [(40, 32, 56), (136, 200, 328), (1032, 1000, 72)])
+def test_tiled_products_of_infinities_and_nan(dev, P, variant, shape):
+    """Infinities and NaN among the operands reach the rows and columns that
+    they reach in the register-staged kernel, and no others."""
+    M, N, K = shape
+    g = torch.Generator(device=dev).manual_seed(M + variant)
+    A = torch.randn(M, K, generator=g, device=dev).to(torch.bfloat16).float()
+    B = torch.randn(K, N, generator=g, device=dev).to(torch.bfloat16).float()
+    A[1, 3], A[M - 1, K - 1], B[K - 1, 2], B[0, N - 1] = float("inf"), float("nan"), float("-inf"), 0.0
+    As = (A if variant != 2 else A.T).contiguous()
+    Bs = (B.T if variant == 0 else B).contiguous()
+    out = []
+    for b16 in (False, True):
+        C = torch.empty(M, N, device=dev)
+        act = torch.empty(M, N, dtype=torch.bfloat16, device=dev)
+        P.gemm_mixed(variant, As.to(torch.bfloat16), True, As.shape[1], Bs.to(torch.bfloat16) if b16 else Bs, b16,
+                     Bs.shape[1], C, N, M, N, K, act=act, act_bf16=True)
+        out.append((C, act))
+    for x, y in zip(*out):
+        assert torch.equal(x.isnan(), y.isnan()) and torch.equal(x.nan_to_num(0.0), y.nan_to_num(0.0))
+    finite = torch.ones(M, N, dtype=torch.bool, device=dev)
+    finite[1], finite[M - 1], finite[:, 2] = False, False, False
+    assert bool(out[1][0][finite].isfinite().all()) and bool(out[1][0][M - 1].isnan().all())
+
+
+@pytest.mark.parametrize("N,B", [(14, 3), (100, 2), (100, 513), (370, 2)])
+def test_penalty_rows_of_infinities_and_nan(dev, P, N, B):
+    """Rows and arc variables that are infinite violate without bound, NaN
+    rows count as no violation, as a comparison with the bounds has it."""
+    from paper_2510_12897_amd import opf as binding
+    cs = synth.network(N, N * 13 // 10, max(2, N // 5), 7)
+    md = binding.Model(cs)
+    L, rho = cs["n_branch"], 10.0
+    g = torch.Generator(device=dev).manual_seed(N + B)
+    C = torch.randn(B, md.m, dtype=torch.float64, device=dev, generator=g)
+    X = torch.randn(B, md.n, dtype=torch.float64, device=dev, generator=g)
+    bal, k = md.block("bal_p")
+    C[0, bal], C[0, bal + 1], C[0, md.m - 1] = float("nan"), 2.5, float("nan")
+    C[B - 1, bal + k - 1] = float("-inf")
+    o, _ = md.block("p")
+    X[0, o], X[0, o + 4 * L - 1] = float("nan"), float("nan")
+    bd = {q: torch.as_tensor(v).to(dev) for q, v in md.bounds().items()}
+
+    def viol(v, lo, hi):
+        return torch.where(v < lo, v - lo, torch.where(v > hi, v - hi, torch.zeros_like(v)))
+
+    pen, cv, W, gpq = (torch.empty(B, q, dtype=torch.float64, device=dev) for q in (1, 1, md.m, 4 * L))
+    binding._check(binding.lib().prox_penalty(md.handle, C.data_ptr(), X.data_ptr(), None, 0.0, rho, B, 0,
+                                              pen.data_ptr(), cv.data_ptr(), W.data_ptr(), gpq.data_ptr(),
+                                              torch.cuda.current_stream().cuda_stream))
+    dv, dq = viol(C, bd["lcon"], bd["ucon"]), viol(X[:, o:o + 4 * L], bd["lvar"][o:o + 4 * L], bd["uvar"][o:o + 4 * L])
+    flow = torch.zeros(md.m, dtype=torch.bool, device=dev)
+    for name in ("p_fr", "q_fr", "p_to", "q_to"):
+        a, n = md.block(name)
+        flow[a:a + n] = True
+    off = torch.where(flow, torch.zeros_like(dv), dv)
+    assert torch.equal(W, 2.0 * rho * off) and torch.equal(gpq, 2.0 * rho * dq)
+    assert torch.equal(cv[:, 0], torch.maximum(dv.abs().amax(1), dq.abs().amax(1)))
+    want = rho * ((off ** 2).sum(1) + (dq ** 2).sum(1))
+    assert torch.equal(pen[:, 0].isinf(), want.isinf()) and bool(want[B - 1].isinf()) and not bool(pen.isnan().any())
+    ok = want.isfinite()
+    assert ((pen[ok, 0] - want[ok]).abs() <= (md.m + 4 * L + 4) * 2.2e-16 * want[ok]).all()
+    md.close()
+
+
+@pytest.mark.parametrize("N,L,B", [(14, 20, 5), (14, 20, 1030), (60, 300, 5), (60, 300, 520), (60, 600, 5)])
+def test_fused_loss_of_infinities_and_nan(dev, P, N, L, B):
+    """Predictions and loads that are infinite or NaN: x, loss and Cvio are the
+    chain's, and the other samples' values and gradients are untouched."""
+    px = P.WarmStartProxy(synth.network(N, L, 6, 11), B=B, width=16, depth=1, seed=2)
+    gen = torch.Generator(device=dev).manual_seed(N + L)
+    loads, _ = px.sample(gen)
+    z = torch.randn(B, 2 * px.N + 2 * px.G, generator=gen, device=dev) * 1.5
+    bad_z, bad_loads = z.clone(), loads.clone()
+    bad_z[0, 2], bad_z[0, px.N + 1], bad_z[1, 0], bad_z[1, 2 * px.N] = float("inf"), float("-inf"), 1e38, -1e38
+    bad_z[2, 1], bad_loads[3, 4], bad_loads[4, px.N + 2] = float("nan"), float("inf"), float("nan")
+    out = []
+    for zz, ll, fused in ((z, loads, True), (bad_z, bad_loads, True), (bad_z, bad_loads, False)):
+        px.pen.fused = fused
+        zb = zz.clone().requires_grad_(True)
+        lb = P._fun("loss").apply(zb, px, ll, True)
+        lb.sum().backward()
+        out.append((lb.detach().clone(), px.pen.last["cvio"].clone(), px.pen.last["x"].clone(), zb.grad))
+    clean, got, chain = out
+    for a, b in zip(got, clean):
+        assert torch.equal(a[5:], b[5:])
+    assert torch.equal(got[2].nan_to_num(7.0), chain[2].nan_to_num(7.0))
+    for a, b in zip(got[:2], chain[:2]):
+        assert torch.equal(a.isnan(), b.isnan()) and torch.equal(a.isinf(), b.isinf())
+        ok = b.isfinite()
+        assert torch.allclose(a[ok], b[ok], rtol=1e-12, atol=1e-15)
+    assert bool(got[0][3].isinf()) and bool(got[0][2].isnan() | got[0][2].isfinite())
+    assert torch.equal(got[3][:2].isnan(), chain[3][:2].isnan())
+    assert float((got[3][:2] - chain[3][:2]).abs().max()) <= 1e-6 * float(chain[3][:2].abs().max())
+    px.close()
