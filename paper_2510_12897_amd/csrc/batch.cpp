@@ -122,7 +122,8 @@ int launch(opf_batch_s* b, const opf::BatchArgs& a0, hipStream_t stream) {
     for (int ph = 0; ph < 2; ph++) {
         if (a[ph].n_items == 0) continue;
         void* args[1] = {&a[ph]};
-        const unsigned lds = ph == 0 && a0.mode == 0 && b->wg_per_cu <= 0 && a0.J && a0.H ? opf::kBranchLds : 0;
+        const unsigned lds =
+            ph == 0 && a0.mode == 0 && b->wg_per_cu <= 0 ? opf::branch_lds(a0.J, a0.H, b->rect, a[ph].n_items) : 0;
         const hipError_t e = hipLaunchKernel(opf::batch_kernel_fn(ph, a0.mode, b->wg_per_cu <= 0, b->rect, b->ext),
                                              dim3(grid[ph]), dim3(opf::kBlock), args, lds, stream);
         if (e != hipSuccess) return hip_err(e, ph == 0 ? "batch branch-phase launch" : "batch bus-phase launch");

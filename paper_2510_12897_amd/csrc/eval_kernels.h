@@ -53,11 +53,18 @@ size_t scratch_bytes(const DevModel& m);
 // Dynamic LDS of a branch phase that writes Jacobian and Hessian, unused: with the 5 KiB
 // of staging it leaves six waves on a compute unit (LDS is dealt in 1280-byte
 // blocks), which together write no further apart than memory takes well.
-// Waves per unit with the items in groups, 48-period set, 200-copy N-1 set and
-// 64-scenario batch: 4 29.1, 43.5, 121.3 us; 5 28.5, 43.7, 113.2; 6 28.3, 44.4,
-// 113.2; 8 29.2, 46.6, 112.5; 24 29.8, 47.2, 115.7.  The Jacobian alone is
-// slower so bounded (batch 44.8 us, 50.7).
+// Waves per unit with the items in groups, 48-period set with storage, 200-copy
+// N-1 set and 64-scenario batch: 4 29.1, 43.5, 121.3 us; 5 28.5, 43.7, 113.2;
+// 6 28.3, 44.4, 113.2; 8 29.2, 46.6, 112.5; 24 29.8, 47.2, 115.7.  The Jacobian
+// alone is slower so bounded (batch 44.8 us, 50.7).  The rectangular form's
+// items write more and take longer, so that a second round hardly begun costs
+// more than the bound gives: 48 periods (2,064 items, 1,536 a round) 34.6 us,
+// 32.9 without; from two rounds on it gains too (200 copies, 4,422 items, 60.3
+// and 63.1; batch 128.8 and 130.9).
 constexpr unsigned kBranchLds = 21 * 1280 - 10 * 64 * 8;
+inline unsigned branch_lds(const double* J, const double* H, bool rect, int32_t items) {
+    return J && H && (!rect || items >= 2 * 6 * 256) ? kBranchLds : 0;
+}
 
 // The batch kernel of phase 0 (branch items) or 1 (bus items) for mode 0
 // (callback set), 1 (J^T v) or 2 (flows, phase 0 only, polar only),

@@ -138,7 +138,7 @@ __device__ __forceinline__ Coef in_service(const Coef& k, const DevModel& m, int
     return m.outage[r] == l ? Coef{0, 0, 0, 0, 0, 0, 0, 0} : k;
 }
 
-// The records of replica r, branches in order (RecSlot).
+// The records of replica r, branches in order (kRecStride).
 __device__ __forceinline__ double* rec_of(const DevModel& m, int32_t r) {
     return m.rec + (int64_t)r * m.L * kRecStride;
 }
@@ -193,9 +193,11 @@ __device__ __forceinline__ int32_t xcd_item(int32_t b, int32_t nb) {
 // each, and memory takes those faster the nearer together the waves in flight
 // write (kBranchLds bounds their number): with one far range per XCD the
 // 64-scenario batch took 122.5 us (117.8 bounded), in groups of 16, 64 and 256
-// 115.6, 115.7 and 117.3 (113.6, 112.5 and 114.4).  Smaller sets keep the
-// ranges, whose neighbours share lines in one L2 (Jacobian alone 44.8 us, 46.2
-// in groups; constraints alone 43.3, 44.2), as does the bus phase.
+// 115.6, 115.7 and 117.3 (113.6, 112.5 and 114.4).  Hessian alone 64.5 us, in
+// ranges 67.2; with the constraints 76.5 and 81.1; rectangular 65.5 and 69.1,
+// 80.7 and 86.2, whole sets 128.8 and 134.8.  Smaller sets keep the ranges,
+// whose neighbours share lines in one L2 (Jacobian alone 44.8 us, 46.2 in
+// groups; constraints alone 43.3, 44.2), as does the bus phase.
 __device__ __forceinline__ int32_t xcd_group_item(int32_t b, int32_t nb) {
     constexpr int32_t kGroup = 64;
     const int32_t full = nb / (kXcd * kGroup) * (kXcd * kGroup);
@@ -548,7 +550,8 @@ __device__ void branch_task(const DevModel& m, const EvalOut& o, int32_t chunk, 
 
 // Phase 1 of the rectangular form: one lane per branch, as branch_task;
 // writes the four flow rows, the two angle rows, the two thermal rows, the
-// arc Hessian diagonals and the half-edge records [D, Bs, D, A, P, Q].
+// arc Hessian diagonals and the branch's record [P, Q, Bs, D, 0, A, Bs, D, P, Q]
+// (from side, shared, to side: dev_model.h).
 template <bool SINGLE>
 __device__ void rbranch_task(const DevModel& m, const EvalOut& o, int32_t chunk, int32_t r, double* stage) {
     const uint32_t l0 = (uint32_t)(chunk * kBlock), l = l0 + threadIdx.x;
@@ -2134,8 +2137,8 @@ hipError_t launch_set_form(const DevModel& m, const EvalOut& o, hipStream_t stre
         return hipGetLastError();
     }
     if (g.phase1() > 0)
-        hipLaunchKernelGGL((branch_kernel<0, RECT, EXT>), dim3(g.phase1()), dim3(kBlock), o.J && o.H ? kBranchLds : 0, stream,
-                           m, o, g);
+        hipLaunchKernelGGL((branch_kernel<0, RECT, EXT>), dim3(g.phase1()), dim3(kBlock),
+                           branch_lds(o.J, o.H, RECT, g.phase1()), stream, m, o, g);
     if (g.phase2() > 0)
         hipLaunchKernelGGL((bus_kernel<0, RECT, EXT>), dim3(g.phase2()), dim3(kBlock), 0, stream, m, o, g);
     return hipGetLastError();
