@@ -214,8 +214,10 @@ void opf_set_allocator(void *(*alloc)(size_t bytes, void *ctx),
  * two launches (branch items leave per-half-edge records that bus items
  * read).  A model keeps its shape for life.  Both shapes give bitwise the
  * same results (no floating-point contraction in the kernels), and so do
- * batches (opf_batch_eval) in either of their shapes.  J^T v always uses
- * two launches.  0 disables the single launch; the default is 4096.
+ * batches (opf_batch_eval) in either of their shapes.  J^T v (opf_jtprod) of
+ * such a model takes one launch too, up to 2048 work items and with an output
+ * apart from x and v, else two; the same bits.  0 disables the single launch;
+ * the default is 4096.
  * OPF_E_ARG for a negative limit. */
 int opf_set_single_launch_limit(int64_t waves);
 
@@ -544,8 +546,8 @@ int prox_loss_fused(opf_model model, const float *z, int B, double va_span, cons
                     double obj_scale, double *loss, double *cvio, double *gz, double *X, double *C, void *stream);
 
 /* 1 when prox_loss_fused takes this model: static, polar, no storage units
- * or devices, and one sample's working set (4N + 2G + 4L doubles) within
- * 64 KiB of LDS; 0 when not; OPF_E_STATE for an invalid handle. */
+ * or devices, and 6N + 4G + 6L + 12 doubles (one sample's working set and two
+ * values per branch) within 64 KiB; 0 when not; OPF_E_STATE for an invalid handle. */
 int prox_loss_fused_fits(opf_model model);
 
 /* dz [B, D] = (float)(wb[b] * gz[b, j]): the backward of prox_loss_fused's

@@ -442,7 +442,7 @@ int prox_penalty(opf_model model, const double* C, const double* X, const double
     if (B < 1 || !C || !X || !pen || !cvio || !W) return set_err(OPF_E_ARG, "bad arguments");
     // without gpq the gradient on p, q stays in the workgroup's LDS: only
     // with vjp (its one reader) and when it fits
-    constexpr int32_t kMaxOnChip = 7680;  // 60 KiB of doubles beside the 4 KiB of reduction arrays
+    constexpr int32_t kMaxOnChip = 7680;  // 60 KiB of doubles; the reduction arrays take 256 bytes
     if (!gpq && (!vjp || model->hm.ly.L * 4 > kMaxOnChip))
         return set_err(OPF_E_ARG, "gpq may be NULL only with vjp and at most %d arc variables", kMaxOnChip);
     DeviceGuard dg(model->device);

@@ -114,8 +114,9 @@ struct ProxPerm {
     const int32_t* gen_pos;  // [G] position of generator k in the bus-ordered generator list
 };
 // Whether the fused loss takes a network of this size: its working set, with
-// two more values per branch, within 64 KiB (two workgroups per compute unit;
-// beyond, the chain of batch launches fills the chip better).
+// two more values per branch, within 64 KiB.  That was the working set, and 64
+// KiB the launch's limit, before the branches' values moved to registers; the
+// networks that are taken stay the same.
 constexpr size_t kFusedLdsMax = 65536;
 bool prox_loss_fused_size(int N, int L, int G);
 // dz (optional, in place of gz) = (float)(w * d loss_b / d z_b).
