@@ -211,7 +211,7 @@ void opf_set_allocator(void *(*alloc)(size_t bytes, void *ctx),
  * whose callback set is at most `waves` 64-lane work items (summed over
  * replicas) evaluates a set in ONE launch, its bus items recomputing the
  * branch terms they need (a small set is latency-bound); larger models use
- * two launches (branch items leave per-half-edge records that bus items
+ * two launches (branch items leave one record per branch that bus items
  * read).  A model keeps its shape for life.  Both shapes give bitwise the
  * same results (no floating-point contraction in the kernels), and so do
  * batches (opf_batch_eval) in either of their shapes.  J^T v (opf_jtprod) of
