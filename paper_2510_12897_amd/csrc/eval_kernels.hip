@@ -39,9 +39,9 @@
 // One-launch shape (plain sets of small models, which are latency-bound):
 // the same items in one launch, dealt round-robin.  Bus half-edge lanes
 // recompute their record from x, y and a slot-ordered copy of the branch
-// terms instead of reading it, so results agree with the two-launch shape to
-// rounding, not bitwise.  The generator chunk whose arrival completes a
-// self-resetting ticket sums the objective partials in index order.
+// terms instead of reading it, with the branch items' arithmetic, so results
+// are bitwise the two-launch shape's.  The generator chunk whose arrival
+// completes a self-resetting ticket sums the objective partials in index order.
 //
 // Branch flows follow the pi model of the PowerModels formulation the paper
 // uses:  F = alpha u^2 + beta w^2 + u w (a cos(th) + b sin(th)),

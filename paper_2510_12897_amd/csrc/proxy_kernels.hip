@@ -845,7 +845,7 @@ __global__ void __launch_bounds__(256) adam_dev4_kernel(float* __restrict__ p, c
 // update those.  Bound by memory: per weight 4 bytes of each part, 24 of
 // parameter and moments, 2 of the BF16 copy.  The gradient itself never
 // reaches memory, and one launch replaces a sum per layer, Adam and the step
-// count's own (4,096-sample step: 348 -> 334 us; this kernel 31 us for 145 MB).  This step's count is the
+// count's own (4,096-sample step on one card, in turn: 348 -> 334 us; this kernel 31 us for 145 MB).  This step's count is the
 // one that its column-sum pass left in the scratch; the launch that has step
 // stores it there, so a step that fails before its update leaves Adam's count
 // as it was.  VEC: 16-byte accesses of parameters and moments.
